@@ -92,6 +92,7 @@ struct Ray {
   float F1, V1, F2, V2;  // u_b(m0 + j) = I_b + F_b + j V_b
   double F1d, V1d, F2d, V2d;  // the same in double (the forward walk's coordinates)
   float A, B, D;     // TOF: vh(j) = A - j B, vl = vh - D (units of sigma sqrt 2)
+  float C;           // TOF: (bin centre - sample) = C - j B
   float L;           // plane length h_a |d| / |d_a|
 };
 
@@ -118,7 +119,7 @@ __host__ __device__ __forceinline__ Ray setup_ray(const GeomDev &g, int id1, int
   Ray r;
   r.nplanes = 0;
   r.m0 = r.a = r.n1 = r.n2 = r.I1 = r.I2 = 0;
-  r.F1 = r.V1 = r.F2 = r.V2 = r.A = r.B = r.D = r.L = 0.0f;
+  r.F1 = r.V1 = r.F2 = r.V2 = r.A = r.B = r.C = r.D = r.L = 0.0f;
   r.F1d = r.V1d = r.F2d = r.V2d = 0.0;
   const float *q1 = g.det + 3 * id1;
   const float *q2 = g.det + 3 * id2;
@@ -233,6 +234,7 @@ __host__ __device__ __forceinline__ Ray setup_ray(const GeomDev &g, int id1, int
   const float B = (float)(dt * g.inv_sr2);
   const float D = (float)(2.0 * edge * g.inv_sr2);
   r.A = A;
+  r.C = (float)((tc - t0) * g.inv_sr2);
   r.B = B;
   r.D = D;
   return r;
@@ -306,82 +308,66 @@ __host__ __device__ __forceinline__ float tof_weight(float vh, float vl, float v
   return fmaxf(w, 0.0f) * inv_norm;
 }
 
-// The weight of one TOF bin as a function of its upper edge vh alone (vl =
-// vh - D, D the bin width; units of sigma sqrt 2), tabulated: it is
-// inv_norm (erf(clamp(vh)) - erf(clamp(vh - D))) with clamp to [-vc, vc],
-// non-zero on (-vc, vc + D) and smooth between the points where an edge
-// meets the truncation (-vc, min(-vc + D, vc), max(-vc + D, vc), vc + D).
-// Each of the three pieces is cut, from its start, into intervals of width
-// exactly 1/64 (a power of two, so that the position (vh - start) * 64 is
-// exact in float32; the last interval of a piece runs past its end and
-// follows the piece's own smooth expression there) with a cubic Hermite
-// interpolant of the exact values and derivatives (error below h^4 max |4th
-// derivative| / 384, about 1e-9 of the peak weight; the float32
-// coefficients and evaluation add about 1e-7).  Evaluating it is an LDS
-// read and three FMAs instead of two erfc.  The table is built per geometry
-// by build_tof_table.
+// The weight of one TOF bin as a function of t = (bin centre - sample) alone
+// (units of sigma sqrt 2; the bin's edges are t + D/2 and t - D/2), tabulated:
+// it is inv_norm (erf(clamp(t + D/2)) - erf(clamp(t - D/2))) with clamp to
+// [-vc, vc], even in t, zero beyond |t| = vc + D/2 and smooth except where an
+// edge meets the truncation, at |t| = |vc - D/2|.  Intervals of width exactly
+// 1/64 (a power of two, so that |t| * 64 is exact in float32) are laid from
+// that point outwards and inwards (the innermost one runs past 0, the
+// outermost past the end; both follow the smooth expression there), each
+// with a cubic Hermite interpolant of the exact values and derivatives (error
+// below h^4 max |4th derivative| / 384, about 1e-9 of the peak weight; the
+// float32 coefficients and evaluation add about 1e-7).  Evaluating it is an
+// LDS read and some ten instructions instead of two erfc, and half the LDS
+// of a table over both signs of t.  The table is built per geometry by
+// build_tof_table.
 constexpr int kTofTabMax = 1024;  // intervals
 constexpr int kTofTabPerUnit = 64;
 
 struct TofTab {
-  float b0, b1, b2, b3;  // piece boundaries
-  int n0, n1, n2;        // intervals of each piece (piece 1 starts at n0, piece 2 at n0 + n1)
+  float tk, te;  // |t| of the kink and of the end of the support
+  int n0, n;     // intervals up to the kink, all intervals
 };
 
 // The table layout of a geometry with TOF (host).
 inline TofTab tof_tab_layout(const GeomDev &g) {
   const double vc = (g.half_win - 0.5 * g.tof_bin) * g.inv_sr2, D = g.tof_bin * g.inv_sr2;
-  const double c[4] = {-vc, fmin(-vc + D, vc), fmax(-vc + D, vc), vc + D};
   TofTab t;
-  t.b0 = (float)c[0];
-  t.b1 = (float)c[1];
-  t.b2 = (float)c[2];
-  t.b3 = (float)c[3];
-  const float b[4] = {t.b0, t.b1, t.b2, t.b3};
-  int n[3];
-  for (int p = 0; p < 3; ++p) {
-    const double w = (double)b[p + 1] - (double)b[p];
-    n[p] = w > 0.0 ? (int)ceil(w * kTofTabPerUnit) : 1;
-  }
-  t.n0 = n[0];
-  t.n1 = n[1];
-  t.n2 = n[2];
+  t.tk = (float)fabs(vc - 0.5 * D);
+  t.te = (float)(vc + 0.5 * D);
+  t.n0 = (int)ceil((double)t.tk * kTofTabPerUnit);
+  t.n = t.n0 + (int)ceil(((double)t.te - (double)t.tk) * kTofTabPerUnit);
   return t;
 }
 
-// The table layout held in registers, uniform over the wavefront (the
-// evaluation selects among its fields per lane; with the struct in kernel
-// argument memory the compiler would load the selected field per lane).
+// The table layout held in registers, uniform over the wavefront.
 __device__ __forceinline__ TofTab tof_tab_uniform(const TofTab &t) {
   TofTab u;
-  u.b0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(t.b0)));
-  u.b1 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(t.b1)));
-  u.b2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(t.b2)));
-  u.b3 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(t.b3)));
+  u.tk = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(t.tk)));
+  u.te = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(t.te)));
   u.n0 = __builtin_amdgcn_readfirstlane(t.n0);
-  u.n1 = __builtin_amdgcn_readfirstlane(t.n1);
-  u.n2 = __builtin_amdgcn_readfirstlane(t.n2);
+  u.n = __builtin_amdgcn_readfirstlane(t.n);
   return u;
 }
 
-__host__ __device__ __forceinline__ int tof_tab_size(const TofTab &t) { return t.n0 + t.n1 + t.n2; }
+__host__ __device__ __forceinline__ int tof_tab_size(const TofTab &t) { return t.n; }
 
-// The tabulated weight at vh (0 outside (b0, b3)); tab: the coefficients
-// {c0, c1, c2, c3} of c0 + s (c1 + s (c2 + s c3)) of every interval, s in
-// [0, 1) the position inside the interval.
-__device__ __forceinline__ float tof_weight_tab(const TofTab &t, const float4 *tab, float vh) {
-  const bool p2 = vh >= t.b2, p1 = vh >= t.b1;
-  const float start = p2 ? t.b2 : (p1 ? t.b1 : t.b0);
-  const int base = p2 ? t.n0 + t.n1 : (p1 ? t.n0 : 0);
-  const int nmax = p2 ? t.n2 : (p1 ? t.n1 : t.n0);
-  const float u = (vh - start) * (float)kTofTabPerUnit;
-  const int i = min(max((int)u, 0), nmax - 1);
-  const float s = u - (float)i;
-  const float4 c = tab[base + i];
+// The tabulated weight at t (0 from te on); tab: the coefficients {c0, c1,
+// c2, c3} of c0 + s (c1 + s (c2 + s c3)) of every interval, s in [0, 1) the
+// position inside the interval.  The interval number is clamped before n0
+// is added, so that any t reads inside the table.
+__device__ __forceinline__ float tof_weight_tab(const TofTab &t, const float4 *tab, float tc) {
+  const float at = fabsf(tc);
+  const float u = fmaf(at, (float)kTofTabPerUnit, -(float)kTofTabPerUnit * t.tk);
+  const float fl = floorf(u);
+  const float s = u - fl;
+  const int i = min((int)fl, t.n - 1 - t.n0) + t.n0;  // fl >= -n0
+  const float4 c = tab[i];
   const float w = fmaf(fmaf(fmaf(c.w, s, c.z), s, c.y), s, c.x);
-  // near the ends of the support the cubic of a weight that falls to 0 can
+  // near the end of the support the cubic of a weight that falls to 0 can
   // round below it
-  return (vh > t.b0 && vh < t.b3) ? fmaxf(w, 0.0f) : 0.0f;
+  return at < t.te ? fmaxf(w, 0.0f) : 0.0f;
 }
 
 // One sample of a ray: plane, lower corner and weights.

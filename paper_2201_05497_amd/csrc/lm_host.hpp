@@ -93,7 +93,9 @@ bool lines_possible(const GeomDev &g);
 int launch_cylindrical(const GeomDev &g, int *flag, hipStream_t st);
 // Sensitivity by line: nothing happens unless *cyl.
 int launch_sens_lines(const GeomDev &g, const int *cyl, float *img, hipStream_t st);
-// Back projection of a long event list by line, guarded by *cyl; `queued`
+// Lists whose back projection goes by line on a cylindrical scanner.
+bool back_by_line(const GeomDev &g, long long n);
+// Back projection of such a list by line, guarded by *cyl; `queued`
 // is false (nothing enqueued) when the list is too short or the
 // temporaries of the sort do not fit.
 int launch_back_lines(const GeomDev &g, const int *cyl, const float *v, const int16_t *ev, long long n, float *img,

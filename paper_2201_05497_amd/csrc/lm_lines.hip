@@ -94,8 +94,9 @@ __device__ __forceinline__ LineLane line_lane(const GeomDev &g, int c1, int c2, 
 
 // Per-LOR coefficients of a line's LOR (rings at z1, z2; TOF centre tc and
 // half-width `edge` of the weight's bin range; value v): with the lane's
-// LOR parameter lam, the TOF argument is vh = A - lam B (units of
-// sigma sqrt 2), vl = vh - D, and the z coordinate in voxels is az + lam bz.
+// LOR parameter lam, the TOF argument is A - lam B (units of sigma sqrt 2),
+// the bin's upper edge vh (vl = vh - D) or, for the tabulated weights, its
+// centre; the z coordinate in voxels is az + lam bz.
 struct Lor {
   double A, B, az, bz;
   float D, c;  // c = v L
@@ -109,11 +110,11 @@ __device__ __forceinline__ void lor_z(const GeomDev &g, double ihz, double z1, d
 }
 
 __device__ __forceinline__ void lor_rest(const GeomDev &g, const LineLane &q, double z1, double z2, double tc,
-                                         double edge, float v, Lor &o) {
+                                         double edge, bool centred, float v, Lor &o) {
   const double dz = z2 - z1;
   const double dn = sqrt(q.dxy2 + dz * dz);
   // t(lam) = (lam - 1/2) dn, vh = (tc + edge - t) / (sigma sqrt 2)
-  o.A = (tc + edge + 0.5 * dn) * g.inv_sr2;
+  o.A = (tc + (centred ? 0.0 : edge) + 0.5 * dn) * g.inv_sr2;
   o.B = dn * g.inv_sr2;
   o.D = (float)(2.0 * edge * g.inv_sr2);
   o.c = v * (float)(q.ha_over_da * dn);
@@ -136,7 +137,7 @@ __device__ __forceinline__ void add_lor(const GeomDev &g, const LineLane &q, con
   if (!q.active) return;
   float c = o.c;
   if (g.tof_on) {
-    const float vh = (float)fma(-q.lam, o.B, o.A);
+    const float vh = (float)fma(-q.lam, o.B, o.A);  // with TAB: the centre
     if constexpr (TAB) {
       c *= tof_weight_tab(tt, tab, vh);
     } else {
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(kLanes) void k_sens_lines(GeomDev g, const int *cyl
         const float z2f = zring(r2);
         pass = dominant_axis(q.fdx, q.fdy, z2f - z1f) != 2;  // z dominant: per-LOR path
         lor_z(g, ihz, z1f, z2f, o);
-        lor_rest(g, q, z1f, z2f, 0.0, edge, 1.0f, o);
+        lor_rest(g, q, z1f, z2f, 0.0, edge, false, 1.0f, o);
       }
       unsigned long long m = __ballot(pass);
       while (m) {
@@ -469,12 +470,13 @@ __global__ __launch_bounds__(kLanes) void k_back_lines(GeomDev g, const int *cyl
       pass = !(floor(fmax(ua, ub)) + 2.0 < (double)zp.zlo ||
                floor(fmin(ua, ub)) - 1.0 >= (double)(zp.zlo + zp.zc));
       if (pass) {
-        lor_rest(g, q, z1f, z2f, k * g.tof_bin, edge, r.v, o);
+        lor_rest(g, q, z1f, z2f, k * g.tof_bin, edge, tab != nullptr, r.v, o);
         if (g.tof_on) {
           // vh decreases along the line: every sample of the chunk lies
           // beyond one edge of the bin's truncated window (a margin for
           // rounding)
-          const double vh_a = o.A - lam_a * o.B, vh_b = o.A - lam_b * o.B;
+          const double up = tab ? edge * g.inv_sr2 : 0.0;  // from the centre to the upper edge
+          const double vh_a = o.A + up - lam_a * o.B, vh_b = o.A + up - lam_b * o.B;
           if (fmin(vh_a, vh_b) - o.D >= g.vclip + 1e-3 || fmax(vh_a, vh_b) <= -g.vclip - 1e-3) pass = false;
         }
       }
@@ -645,14 +647,14 @@ __device__ __forceinline__ void sheet_corners(const GeomDev &g, const FwdLine &q
 
 // A LOR of a line (ring z's z1, z2 and TOF bin k in the line's orientation):
 // the planes it can touch, m0 .. m1 (m1 < m0: none), its TOF argument vh0 +
-// j dvh and z coordinate u20 + j du2 (voxels) at plane m0 + j, and its plane
+// j dvh (the bin's upper edge; tc0 + j dvh its centre) and z coordinate u20 + j du2 (voxels) at plane m0 + j, and its plane
 // length L.  The TOF argument is stepped in float from its double value at
 // m0 (|vh| stays below a few units, so its float error is a few 1e-7 sigma,
 // as in the per-event walk); z takes one double FMA per sample (in float, j
 // dz a few tens of voxels along would carry 1e-6 voxel errors).
 struct LineLor {
   int m0, m1;
-  float vh0, dvh;
+  float vh0, tc0, dvh;
   double u20, du2;
   float L;
 };
@@ -683,13 +685,14 @@ __device__ __forceinline__ LineLor line_lor(const GeomDev &g, const FwdLine &q, 
   }
   LineLor o;
   o.L = (float)(q.ha_over_da * dn);
-  o.vh0 = o.dvh = 0.0f;
+  o.vh0 = o.tc0 = o.dvh = 0.0f;
   o.u20 = o.du2 = 0.0;
   if (hi >= lo) {
     o.m0 = (int)lo;
     o.m1 = (int)hi;
     const double lam_lo = fma(lo, q.dlam, q.lam0);
     o.vh0 = (float)(A - lam_lo * B);
+    o.tc0 = (float)((k * g.tof_bin + 0.5 * dn) * g.inv_sr2 - lam_lo * B);
     o.dvh = (float)(-q.dlam * B);
     o.u20 = fma(lam_lo, bz, az);
     o.du2 = q.dlam * bz;
@@ -708,7 +711,7 @@ __device__ __forceinline__ float line_weight(const GeomDev &g, const LineLor &o,
     const float vh = fmaf((float)j, o.dvh, o.vh0);
     return tof_weight(vh, vh - D, g.vclip, g.inv_norm);
   } else if constexpr (TM == kTofTable) {
-    return tof_weight_tab(tt, tab, fmaf((float)j, o.dvh, o.vh0));
+    return tof_weight_tab(tt, tab, fmaf((float)j, o.dvh, o.tc0));
   } else {
     return 1.0f;
   }
@@ -879,38 +882,24 @@ __global__ __launch_bounds__(kFwdLineBlock) void k_fwd_lines(GeomDev g, const in
 
 
 // Coefficients of the TOF table (one interval per thread; see TofTab):
-// values and derivatives of the piece's own smooth expression at both ends
-// of the interval, in double.
+// values and derivatives of the smooth expression at both ends of the
+// interval, in double.
 __global__ __launch_bounds__(256) void k_tof_table(TofTab t, double vc, double D, double inv_norm, float4 *tab) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= tof_tab_size(t)) return;
-  int j;
-  float start, end;
-  if (i < t.n0) {
-    j = i;
-    start = t.b0;
-    end = t.b1;
-  } else if (i < t.n0 + t.n1) {
-    j = i - t.n0;
-    start = t.b1;
-    end = t.b2;
-  } else {
-    j = i - t.n0 - t.n1;
-    start = t.b2;
-    end = t.b3;
-  }
-  // the evaluation maps s in [0, 1) to vh = start + (j + s) / kTofTabPerUnit
-  const double a = start + (double)j / kTofTabPerUnit, b = start + (double)(j + 1) / kTofTabPerUnit;
-  // the piece's expression (decided at the piece's middle, also for an
-  // interval that runs past the piece's end)
-  const double mid = 0.5 * ((double)start + (double)end);
-  const bool up = mid < vc;       // the upper edge inside the truncation
-  const bool lo = mid - D > -vc;  // the lower edge inside the truncation
+  // the evaluation maps s in [0, 1) to |t| = tk + (i - n0 + s) / kTofTabPerUnit
+  const double a = t.tk + (double)(i - t.n0) / kTofTabPerUnit, b = t.tk + (double)(i + 1 - t.n0) / kTofTabPerUnit;
+  // the expression on the interval's side of the kink: with the bin narrower
+  // than the truncation both edges are inside it below the kink and the
+  // upper one is outside above; with a wider bin both are outside below
+  const bool in = i < t.n0 && 0.5 * D < vc;
+  const bool up = in, lo = in || i >= t.n0;
   const double eu = erf(vc), el = erf(-vc);
-  auto f = [&](double v) { return inv_norm * ((up ? erf(v) : eu) - (lo ? erf(v - D) : el)); };
+  auto f = [&](double v) { return inv_norm * ((up ? erf(v + 0.5 * D) : eu) - (lo ? erf(v - 0.5 * D) : el)); };
   auto df = [&](double v) {
     const double two_over_sqrt_pi = 1.1283791670955126;
-    return inv_norm * two_over_sqrt_pi * ((up ? exp(-v * v) : 0.0) - (lo ? exp(-(v - D) * (v - D)) : 0.0));
+    const double vu = v + 0.5 * D, vl = v - 0.5 * D;
+    return inv_norm * two_over_sqrt_pi * ((up ? exp(-vu * vu) : 0.0) - (lo ? exp(-vl * vl) : 0.0));
   };
   const double h = b - a, fa = f(a), fb = f(b), da = h * df(a), db = h * df(b);
   tab[i] = make_float4((float)fa, (float)da, (float)(3.0 * (fb - fa) - 2.0 * da - db),
@@ -1096,12 +1085,18 @@ int launch_fwd_lines(const GeomDev &g, const int *cyl, const float *x, const int
 // a few tens of events do on the per-event path).
 constexpr long long kMinEventsPerLine = 64;
 
+bool back_by_line(const GeomDev &g, long long n) {
+  const long long nlines = (long long)g.n_cry * (g.n_cry - 1) / 2;
+  // the records hold rings in 12 bits and the TOF bin in 8
+  if (!lines_possible(g) || g.n_ring > 4096 || g.n_tof > 255) return false;
+  return n >= kMinEventsPerLine * nlines && n < (1LL << 31) && nlines <= (long long)kGroupMaxBuckets;
+}
+
 int launch_back_lines(const GeomDev &g, const int *cyl, const float *v, const int16_t *ev, long long n, float *img,
                       hipStream_t st, bool &queued) {
   queued = false;
   const long long nlines = (long long)g.n_cry * (g.n_cry - 1) / 2;
-  if (!lines_possible(g) || g.n_ring > 4096 || g.n_tof > 255) return LM_OK;
-  if (n < kMinEventsPerLine * nlines || n >= (1LL << 31) || nlines > (long long)kGroupMaxBuckets) return LM_OK;
+  if (!back_by_line(g, n)) return LM_OK;
   int *key = nullptr;
   unsigned *off = nullptr;
   LineRec *rec = nullptr, *recu = nullptr;

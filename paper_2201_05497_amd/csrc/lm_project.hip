@@ -17,6 +17,7 @@
 #include "lm_device.hpp"
 #include "lm_host.hpp"
 #include "lm_image.hpp"
+#include "lm_segs.hpp"
 
 using namespace lmk;
 
@@ -378,22 +379,27 @@ int launch_fwd(const GeomDev &g, const float *x, const int16_t *ev, long long n,
 }
 int launch_back(const GeomDev &g, const float *v, const int16_t *ev, long long n, float *img, hipStream_t st) {
   if (n == 0) return LM_OK;
-  DevFlag cyl;
   bool queued = false;
-  if (lines_possible(g)) {
+  if (back_by_line(g, n)) {
+    DevFlag cyl;
     if (int rc = cyl.alloc(st)) return rc;
     if (int rc = launch_cylindrical(g, cyl.p, st)) return rc;
     if (int rc = launch_back_lines(g, cyl.p, v, ev, n, img, st, queued)) return rc;
+    // queued on a scanner that is not cylindrical: the per-event kernel
+    // takes the list
+    if (queued) return back_impl(g, cyl.p, v, CallerEvents{ev}, n, img, st);
   }
-  // the per-event kernel takes the list when the line path was not queued,
-  // or was queued on a scanner that is not cylindrical
-  return back_impl(g, queued ? cyl.p : nullptr, v, CallerEvents{ev}, n, img, st);
+  if (int rc = launch_back_tiles(g, v, ev, nullptr, n, img, st, queued)) return rc;
+  return queued ? LM_OK : back_impl(g, nullptr, v, CallerEvents{ev}, n, img, st);
 }
 int launch_fwd_rec(const GeomDev &g, const float *x, const int4 *rec, long long n, float *out, hipStream_t st) {
   return fwd_impl(g, x, PlanEvents{rec}, n, out, st);
 }
 int launch_back_rec(const GeomDev &g, const float *v, const int4 *rec, long long n, float *img, hipStream_t st) {
-  return back_impl(g, nullptr, v, PlanEvents{rec}, n, img, st);
+  if (n == 0) return LM_OK;
+  bool queued = false;
+  if (int rc = launch_back_tiles(g, v, nullptr, rec, n, img, st, queued)) return rc;
+  return queued ? LM_OK : back_impl(g, nullptr, v, PlanEvents{rec}, n, img, st);
 }
 
 int launch_sens(const GeomDev &g, float *img, hipStream_t st) {

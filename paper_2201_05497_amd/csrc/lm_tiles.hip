@@ -218,7 +218,7 @@ __global__ __launch_bounds__(kScanB) void k_block_scan(const unsigned *in, long 
 struct TileRay {
   int4 p;    // {m0, nplanes, a, I1}
   int4 q;    // {I2, F1, V1, F2} (floats as bits)
-  float4 r;  // {V2, A, B, L}
+  float4 r;  // {V2, A (with the TOF table C), B, L}
 };
 
 // Phase 1: per event (8 lanes), the forward projection, the dual prox (the
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kBlock1) void k_tile_fwd(GeomDev g, TileGeom tg, in
     TileRay t;
     t.p = make_int4(r.m0, r.nplanes, r.a, r.I1);
     t.q = make_int4(r.I2, __float_as_int(r.F1), __float_as_int(r.V1), __float_as_int(r.F2));
-    t.r = make_float4(r.V2, r.A, r.B, r.L);
+    t.r = make_float4(r.V2, TAB ? r.C : r.A, r.B, r.L);
     rays[threadIdx.x] = t;
   }
   if constexpr (TAB) {
@@ -560,15 +560,6 @@ constexpr long long kChunk = 1LL << 28;
 
 namespace lmk {
 
-TileGeom tile_geom(const int n[3]) {
-  TileGeom t;
-  t.ntx = (n[0] + kTE - 1) / kTE;
-  t.nty = (n[1] + kTE - 1) / kTE;
-  t.ntz = (n[2] + kTE - 1) / kTE;
-  t.ntiles = t.ntx * t.nty * t.ntz;
-  return t;
-}
-
 // 3D plans (4x4x4 bricks) whose events visit few enough planes for the
 // register cache of phase 1.
 static int j8_for(int maxp) { return (maxp + kTE - 1 + kLanes1 - 1) / kLanes1; }
@@ -580,7 +571,7 @@ bool tiles_supported(const GeomDev &g) {
 
 size_t tile_bytes_bound(const GeomDev &g, long long n, int nsub) {
   if (!tiles_supported(g) || n <= 0) return 0;
-  const TileGeom tg = tile_geom(g.n);
+  const TileGeom tg = tile_geom(g.n, kTE);
   if ((n + nsub - 1) / nsub < kMinEventsPerTile * tg.ntiles) return 0;
   const int maxp = lmh::max_planes(g, W_BIN);
   // tiles a chunk of 8 planes along axis a can reach along axis b: the
@@ -613,7 +604,7 @@ int build_tiles(const GeomDev &g, const int4 *rec, const std::vector<int> &off, 
   const int nsub = (int)off.size() - 1;
   const long long N = off.back();
   if (N == 0) return LM_OK;
-  const TileGeom tg = tile_geom(g.n);
+  const TileGeom tg = tile_geom(g.n, kTE);
   long long nlargest = 0;
   for (int i = 0; i < nsub; ++i) nlargest = std::max<long long>(nlargest, off[i + 1] - off[i]);
   if (nlargest < kMinEventsPerTile * tg.ntiles) return LM_OK;

@@ -10,14 +10,9 @@
 #include <vector>
 
 #include "lm_device.hpp"
+#include "lm_segs.hpp"
 
 namespace lmk {
-
-// Tiles of 8 x 8 x 8 voxels (2 x 2 x 2 bricks of the plan's layout) over an
-// image with 4x4x4-voxel bricks.
-struct TileGeom {
-  int ntx, nty, ntz, ntiles;
-};
 
 // One segment as phase 2 reads it (64 bytes, one memory sector; written by
 // phase 1, the records of an event in a row): the in-plane coordinates of
@@ -51,7 +46,6 @@ struct TilePlan {
 };
 
 bool tiles_supported(const GeomDev &g);
-TileGeom tile_geom(const int n[3]);
 
 // Upper bound of the device bytes the tile path of a plan of n events in
 // nsub subsets holds (segments, offsets, launch order, the phase-1 records
