@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kBackBlock) void k_list_back(GeomDev g, TileGeom tg
   extern __shared__ float4 stab[];
   const unsigned ni = nitems[0];
   if (blockIdx.x >= ni) return;
-  if constexpr (TM == kSegTable)
+  if constexpr (TM == kTofTable)
     for (int i = threadIdx.x; i < tof_tab_size(tt); i += kBackBlock) stab[i] = tab[i];
   const TofTab tu = tof_tab_uniform(tt);
   const float D = tof_bin_width(g);
@@ -255,7 +255,7 @@ int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const
   if (tg.ntiles > kMaxListTiles) return LM_OK;
   const int maxp = lmh::max_planes(g, W_BIN);
   const long long pe = segs_per_event(g, maxp, kTL);
-  const long long batch = std::min(std::min(n, kMaxSegEvents), kListSegBytes / (4 * pe));
+  const long long batch = std::min(std::min(n, 1LL << 30), kListSegBytes / (4 * pe));
   if (batch < kMinListEvents) return LM_OK;  // very unequal voxel sides: too many tiles per event to plan for
   const long long items = batch * pe / kItemMin + tg.ntiles;
   // one allocation: rays, items, segment numbers, values, tot and fill, off, nitems
@@ -299,9 +299,9 @@ int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const
 #define LM_LB(TM_)                                                                                                  \
   hipLaunchKernelGGL((k_list_back<TM_>), dim3(kBackGrid), dim3(kBackBlock), tlds, st, g, tg, off, item, nitems, seg, \
                      rays, val, tt, tab, img)
-    if (!g.tof_on) LM_LB(kSegNoTof);
-    else if (tab) LM_LB(kSegTable);
-    else LM_LB(kSegErfc);
+    if (!g.tof_on) LM_LB(kTofNone);
+    else if (tab) LM_LB(kTofTable);
+    else LM_LB(kTofErfc);
 #undef LM_LB
     e = hipGetLastError();
   }

@@ -604,9 +604,6 @@ size_t fwd_sheet_bytes(const GeomDev &g) {
   return (nm * sheet_row(g.n[2]) + 3 * nm) * sizeof(float);
 }
 
-// TOF weights of the walks: none, the erfc evaluation, or the table.
-enum TofMode { kTofNone = 0, kTofErfc = 1, kTofTable = 2 };
-
 // LDS of a line block: the TOF table (when given), the sheet [plane][z]
 // (rows of sheet_row(nz) floats), each plane's two transaxial corners as
 // layout indices at z = 0 (-1: outside the image) and the fraction f1.
@@ -748,7 +745,7 @@ __device__ __forceinline__ float fwd_event(const GeomDev &g, const float *__rest
   if (!decode_event(g, ev, id1, id2, k)) return 0.0f;
   const RayPack pk = pack_ray(setup_ray(g, id1, id2, k, W_BIN, 1 << 20));
   if (pk.p.y <= 0) return 0.0f;
-  const float acc = g.tof_on ? fwd_walk<true>(g, x, pk, D, gl) : fwd_walk<false>(g, x, pk, D, gl);
+  const float acc = g.tof_on ? fwd_walk<true, 8>(g, x, pk, D, gl) : fwd_walk<false, 8>(g, x, pk, D, gl);
   return __int_as_float(pk.q.w) * acc;
 }
 

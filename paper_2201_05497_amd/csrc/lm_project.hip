@@ -63,41 +63,47 @@ struct SortedEvents {
   __device__ __forceinline__ long long slot(long long e) const { return order[e]; }
 };
 
-// Lanes per event of the forward projector, and events per launch (2^19
-// blocks).
-constexpr int kFwdLanes = 8;
+// Events per launch of the forward projector (2^19 blocks of 64 events per
+// wavefront).
 constexpr long long kFwdLaunch = 1LL << 27;
 
-// Forward projection.  A wavefront takes 64 consecutive events of the
-// source: lane e first sets up the ray of event e (the double-precision
-// set-up runs once per event rather than once per lane of a group) and
-// stores it in LDS; then, in eight rounds, each group of kFwdLanes = 8 lanes
-// walks the planes of one event (lane l of the group from the brick
-// boundary at or below the first plane, every 8th plane), and lane e of the
+// Forward projection.  A wavefront takes EPW consecutive events of the
+// source: lane e < EPW first sets up the ray of event e (the
+// double-precision set-up runs once per event rather than once per lane of
+// a group) and stores it in LDS; then, in rounds, each group of LPE lanes
+// walks the planes of one event (lane l of the group from the brick boundary
+// at or below the first plane, every LPE-th plane), and lane e of the
 // wavefront collects event e's sum for one store per lane.
-template <class Src>
+//
+// Bound on long lists by the L1's look-ups: the corners of a wavefront's 64
+// samples lie on lines of their own, which the L1 serves at 1.4 lanes per
+// clock and CU, the rate this kernel reaches (2.7 ms for 1e7 events on
+// 200x200x96).  Tabulated TOF weights, 40 of 130 instructions per sample
+// fewer, took 3.0 ms.
+template <class Src, bool TOF, int LPE, int EPW>
 __global__ __launch_bounds__(kBlock) void k_fwd(GeomDev g, const int *skip, const float *__restrict__ x, Src src,
                                                 long long n, float *__restrict__ out) {
-  static_assert(kFwdLanes == 8, "eight groups of eight lanes per wavefront");
-  __shared__ RayPack rays[kBlock];
+  constexpr int kGroups = 64 / LPE, kRounds = EPW / kGroups, kPerBlock = EPW * (kBlock / 64);
+  static_assert(kRounds * kGroups == EPW && EPW <= 64, "whole rounds");
+  __shared__ RayPack rays[kPerBlock];
   if (skip && *skip) return;  // the list went to the path by line
-  const int lane = threadIdx.x & 63;
-  const int wbase = threadIdx.x & ~63;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   long long blk = blockIdx.x;
   if constexpr (Src::kXcdOrder) {  // gridDim.x is a multiple of 8
     const long long per = gridDim.x / 8;
     blk = (blk % 8) * per + blk / 8;
   }
-  if (blk * kBlock + wbase >= n) return;  // the whole wavefront is past the end
-  const long long e = blk * kBlock + threadIdx.x;
-  {
+  const long long e0 = blk * kPerBlock + wv * EPW, e = e0 + lane;
+  if (e0 >= n) return;  // the whole wavefront is past the end
+  RayPack *wrays = rays + wv * EPW;
+  if (lane < EPW) {
     // every field defined on every path: lanes past the end and invalid
     // events store an empty ray, and only valid events reach the set-up
     // (which reads the crystal table at the decoded ids)
     RayPack pk = empty_ray();
     int id1 = 0, id2 = 0, k = 0;
     if (e < n && src.get(g, e, id1, id2, k)) pk = pack_ray(setup_ray(g, id1, id2, k, W_BIN, 1 << 20));
-    rays[threadIdx.x] = pk;
+    wrays[lane] = pk;
   }
   // LDS operations of one wavefront complete in order; the fences keep the
   // compiler from moving the reads above the writes
@@ -105,19 +111,18 @@ __global__ __launch_bounds__(kBlock) void k_fwd(GeomDev g, const int *skip, cons
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const float D = tof_bin_width(g);
-  const int gl = lane & 7, grp = lane >> 3;
-  float mine = 0.0f, L = 0.0f;
-  for (int round = 0; round < 8; ++round) {
-    const RayPack pk = rays[wbase + 8 * round + grp];
+  const int gl = lane % LPE, grp = lane / LPE;
+  float mine = 0.0f;
+  for (int round = 0; round < kRounds; ++round) {
+    const RayPack pk = wrays[kGroups * round + grp];
     float acc = 0.0f;
-    if (pk.p.y > 0) acc = g.tof_on ? fwd_walk<true>(g, x, pk, D, gl) : fwd_walk<false>(g, x, pk, D, gl);
-    acc = group_sum<8>(acc);
-    // lanes 8 round .. 8 round + 7 take the sums of groups 0 .. 7
-    const float got = __shfl(acc, 8 * gl);
-    if (grp == round) mine = got;
+    if (pk.p.y > 0) acc = fwd_walk<TOF, LPE>(g, x, pk, D, gl);
+    acc = group_sum<LPE>(acc);
+    // lanes kGroups round .. take the sums of the groups
+    const float got = __shfl(acc, LPE * (lane % kGroups));
+    if (lane / kGroups == round) mine = got;
   }
-  L = __int_as_float(rays[threadIdx.x].q.w);
-  if (e < n) out[src.slot(e)] = L * mine;
+  if (lane < EPW && e < n) out[src.slot(e)] = __int_as_float(wrays[lane].q.w) * mine;
 }
 
 // Per-wavefront LDS staging of the interleaved scatter (4 wavefronts per
@@ -324,20 +329,32 @@ int max_planes(const lmk::GeomDev &g, int mode) {
 
 namespace lmk {
 
+template <class Src, int LPE, int EPW>
+static int fwd_launch(const GeomDev &g, const float *x, Src src, long long n, float *out, hipStream_t st,
+                      const int *skip) {
+  constexpr int kPerBlock = EPW * (kBlock / 64);
+  for (long long o = 0; o < n; o += kFwdLaunch) {
+    const long long m = std::min(kFwdLaunch, n - o);
+    unsigned nb = (unsigned)((m + kPerBlock - 1) / kPerBlock);
+    if (Src::kXcdOrder) nb = (nb + 7) / 8 * 8;
+    // sorted sources write out[order[e]]: out is the whole list's
+    float *o_out = Src::kXcdOrder ? out : out + o;
+    if (g.tof_on)
+      hipLaunchKernelGGL((k_fwd<Src, true, LPE, EPW>), dim3(nb), dim3(kBlock), 0, st, g, skip, x, src.offset(o), m,
+                         o_out);
+    else
+      hipLaunchKernelGGL((k_fwd<Src, false, LPE, EPW>), dim3(nb), dim3(kBlock), 0, st, g, skip, x, src.offset(o), m,
+                         o_out);
+    LM_TRY_HIP(hipGetLastError());
+  }
+  return LM_OK;
+}
+
 template <class Src>
 static int fwd_impl(const GeomDev &g, const float *x, Src src, long long n, float *out, hipStream_t st,
                     const int *skip = nullptr) {
   if (n == 0) return LM_OK;
-  for (long long o = 0; o < n; o += kFwdLaunch) {
-    const long long m = std::min(kFwdLaunch, n - o);
-    unsigned nb = blocks_for(m, 1);
-    if (Src::kXcdOrder) nb = (nb + 7) / 8 * 8;
-    // sorted sources write out[order[e]]: out is the whole list's
-    hipLaunchKernelGGL((k_fwd<Src>), dim3(nb), dim3(kBlock), 0, st, g, skip, x, src.offset(o), m,
-                       Src::kXcdOrder ? out : out + o);
-    LM_TRY_HIP(hipGetLastError());
-  }
-  return LM_OK;
+  return fwd_launch<Src, 8, 64>(g, x, src, n, out, st, skip);
 }
 
 // Grid of the grid-stride scattering kernels: enough wavefronts to fill the

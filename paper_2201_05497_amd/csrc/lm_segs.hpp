@@ -106,9 +106,6 @@ struct AccShape {
   static_assert(Y % 2 == 1 && Z % 2 == 1, "odd strides");
 };
 
-// TOF weights of a kernel: none, the erfc evaluation, or the table in LDS.
-enum SegTof { kSegNoTof = 0, kSegErfc = 1, kSegTable = 2 };
-
 __device__ __forceinline__ void lds_add(char *p, float v) {
   __hip_atomic_fetch_add((double *)p, (double)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -161,9 +158,9 @@ __device__ __forceinline__ void add_sample(const GeomDev &g, const TileLane<TE> 
   // on the ray, and a corner in the tile
   if (on && (unsigned)j < (unsigned)seg_np(s) && l1 >= -1.0f && l1 < (float)TE && l2 >= -1.0f && l2 < (float)TE) {
     float v = val;
-    if constexpr (TM != kSegNoTof) {
+    if constexpr (TM != kTofNone) {
       const float tc = fmaf(-fj, s.b.w, s.b.z);
-      if constexpr (TM == kSegTable) {
+      if constexpr (TM == kTofTable) {
         v *= tof_weight_tab(tu, tab, tc);
       } else {
         const float vh = fmaf(0.5f, D, tc);
@@ -188,15 +185,7 @@ __device__ __forceinline__ void add_sample(const GeomDev &g, const TileLane<TE> 
 // them and every nw-th after.  A segment's number is loaded two steps and its
 // ray one step before they are used, in that order, so that waiting for a
 // number leaves the rays in flight; two steps per turn of the loop, so that
-// no register is copied (a copy would wait for the loads).  Byte offsets are
-// 32 bits: at most kMaxSegEvents rays.
-constexpr long long kMaxSegEvents = 1LL << 26;
-
-template <class T>
-__device__ __forceinline__ T load_at(const void *p, unsigned byte) {
-  return *(const T *)((const char *)p + byte);
-}
-
+// no register is copied (a copy would wait for the loads).  cnt < 2^28.
 template <int TM, int TE>
 __device__ __forceinline__ void add_segments(const GeomDev &g, const TileLane<TE> &t, const unsigned *__restrict__ seg,
                                              int cnt, const SegRay *__restrict__ rays,
@@ -207,26 +196,26 @@ __device__ __forceinline__ void add_segments(const GeomDev &g, const TileLane<TE
   if (k0 >= cnt) return;
   // numbers past the end are clamped to the last one; their samples are not added
   const unsigned lim = 4u * (unsigned)(cnt - 1);
-  auto num = [&](unsigned byte) { return load_at<unsigned>(seg, min(byte, lim)); };
+  auto num = [&](unsigned byte) { return *(const unsigned *)((const char *)seg + min(byte, lim)); };
   auto ray = [&](unsigned e) {
     SegRay r;
-    r.a = load_at<int4>(rays, 32u * e);
-    r.b = load_at<float4>(rays, 32u * e + 16u);
+    r.a = rays[e].a;
+    r.b = rays[e].b;
     return r;
   };
   unsigned byte = 4u * (unsigned)(k0 + sub);
   const unsigned bstep = 4u * (unsigned)step;
   unsigned eA = num(byte), eB = num(byte + bstep);
   SegRay rA = ray(eA);
-  float vA = load_at<float>(val, 4u * eA);
+  float vA = val[eA];
   for (int k = k0; k < cnt; k += 2 * step, byte += 2 * bstep) {
     eA = num(byte + 2 * bstep);
     const SegRay rB = ray(eB);
-    const float vB = load_at<float>(val, 4u * eB);
+    const float vB = val[eB];
     add_sample<TM, TE>(g, t, rA, vA, byte <= lim, D, tu, tab, (char *)acc);
     eB = num(byte + 3 * bstep);
     rA = ray(eA);
-    vA = load_at<float>(val, 4u * eA);
+    vA = val[eA];
     add_sample<TM, TE>(g, t, rB, vB, byte + bstep <= lim, D, tu, tab, (char *)acc);
   }
 }

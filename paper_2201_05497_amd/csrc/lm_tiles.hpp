@@ -14,43 +14,26 @@
 
 namespace lmk {
 
-// One segment as phase 2 reads it (64 bytes, one memory sector; written by
-// phase 1, the records of an event in a row): the in-plane coordinates of
-// the event's samples on the tile's 8 planes along its dominant axis are
-// u_p = G + p V (p = 0..7; G the coordinate at the tile's first plane), and
-// for each plane p the sample's value v[p] = cf w_j (cf = L dy / mu; 0
-// outside the ray) and meta[p] = 0 when no corner of the sample adds to the
-// tile, else (tile-local index of corner 0 + 128) | (corner mask << 10) |
-// (dominant axis << 14), the mask having bit c set for each bilinear corner
-// c inside both the tile and the image.
-struct __align__(64) TileRec {
-  float4 h;  // {G1, V1, G2, V2}
-  float v[8];
-  unsigned short meta[8];
-};
-
 // Per-plan state of the tile path; `on` false: the per-event path runs.
 struct TilePlan {
   bool on = false;
   TileGeom tg{};
   int maxp = 0;                  // plane bound of every event (setup_ray's clamp)
-  long long nseg = 0;            // segments of all subsets
-  long long rec_max = 0;         // segments of the largest subset
   long long *seg_off = nullptr;  // [nsub * ntiles + 1] first entry of seg of (subset, tile), all subsets in a row
-  unsigned long long *eoff = nullptr;  // [N + 1] first record of each stored event (records of an event in a row)
-  unsigned *seg = nullptr;       // record numbers (relative to the subset's first) of every tile, by subset and tile
+  unsigned *seg = nullptr;       // events (relative to the subset's first) of every tile, by subset and tile
   int *order = nullptr;          // tiles by decreasing load (launch order of phase 2)
-  TileRec *rec = nullptr;        // [rec_max] segments of the subset being updated
+  SegRay *rays = nullptr;        // rays and back projected values of the subset being updated
+  float *cf = nullptr;
   TofTab tt{};                   // layout of the tabulated TOF weights
-  float4 *tab = nullptr;         // the table (nullptr: phase 1 evaluates erfc)
+  float4 *tab = nullptr;         // the table (nullptr: erfc, or no TOF)
 };
 
 bool tiles_supported(const GeomDev &g);
 
 // Upper bound of the device bytes the tile path of a plan of n events in
-// nsub subsets holds (segments, offsets, launch order, the phase-1 records
-// of the largest subset) plus its temporaries at creation; 0 when the
-// geometry does not qualify.  Each event has at most one segment per tile
+// nsub subsets holds (segments, offsets, launch order, the rays and values of
+// the largest subset) plus its temporaries at creation; 0 when the geometry
+// does not qualify.  Each event has at most one segment per tile
 // that its corners reach on 8 consecutive planes.
 size_t tile_bytes_bound(const GeomDev &g, long long n, int nsub);
 
@@ -65,10 +48,11 @@ int build_tiles(const GeomDev &g, const int4 *rec, const std::vector<int> &off, 
                 std::vector<void *> &owned, hipStream_t st);
 
 // Phase 1 of a data update of the subset stored at positions [o, o + n):
-// forward projection, dual prox, and the subset's segment records.
+// forward projection, dual prox, and the subset's rays and back projected
+// values.
 int launch_tile_fwd(const GeomDev &g, const TilePlan &tp, const float *x, const int4 *rec, const float *S,
                     const float *mu, float *cdual, long long o, long long n, hipStream_t st);
-// Phase 2: back projection by tile; dz_out != NULL writes dz (every voxel of
+// Phase 2: back projection of these by tile; dz_out != NULL writes dz (every voxel of
 // the layout) instead of the z / zbar / primal step.
 int launch_tile_back(const GeomDev &g, const TilePlan &tp, int subset, float *z, float *x, const float *T,
                      float *zbar, float *dz_out, float inv_p, bool fuse, hipStream_t st);
