@@ -1,17 +1,19 @@
-"""GPU parity of the kernels whose split depends on the number of image
-tiles, at the edges of their ranges, against the FP64 oracle: the data update
-of a plan (512 or 256 threads per 8x8x8 tile).  Tolerance as for every
-iterate (1e-4)."""
+"""GPU parity of the kernels whose split depends on the length of the list or
+on the number of image tiles, at the edges of their ranges, against the FP64
+oracle: the forward projection (2, 8, 16 or 64 events per wavefront) and the
+data update of a plan (512 or 256 threads per 8x8x8 tile).  Tolerances as
+for every projection (1e-5) and iterate (1e-4)."""
 import numpy as np
 import pytest
 import torch
 
 import lmsynth
 import oracle
-from tests.helpers import img_err, report
+from tests.helpers import img_err, proj_err, report, smooth_image
 
 pytestmark = pytest.mark.gpu
 
+PROJ_TOL = 1e-5
 ITER_TOL = 1e-4
 
 
@@ -30,6 +32,28 @@ def _geometry(P, n, h, tof, n_cry=96, n_ring=12):
     args = (lmsynth.det_table(sc), n_cry, n_ring, n, h, 9, 12.0, 30.0, 3.0, tof)
     p = lmsynth.Problem("t", sc, lmsynth.ImageGeom(n, h), lmsynth.TOF(9, 12.0, 30.0, 3.0, tof), 1, 1, 0.0)
     return p, P.Geometry(*args, device="cuda"), oracle.Geometry(*args)
+
+
+@pytest.mark.parametrize("n,h,tof", [
+    ((17, 15, 5), (2.0, 2.6, 3.1), True),
+    ((33, 31, 1), (2.0, 2.0, 2.0), True),    # one slice
+    ((15, 18, 7), (2.0, 2.0, 2.0), False),   # no TOF: more planes than lanes of an event
+])
+def test_forward_at_the_edges_of_its_splits(P, n, h, tof):
+    p, Gg, Go = _geometry(P, n, h, tof)
+    ev = lmsynth.random_events(p, (1 << 19) + 37, seed=61, min_sep=1)
+    ev[3], ev[4] = [3, 12, 7, 0, 0], [5, 0, 5, 0, 0]  # no detector, no line: 0
+    x = smooth_image(Go.shape, 62)
+    xd, evd = torch.as_tensor(x, dtype=torch.float32, device="cuda"), Gg.events(ev)
+    first = np.setdiff1d(np.arange(4096), [3, 4])
+    for m in (1, 3, (1 << 14) - 1, (1 << 14) + 5, (1 << 16) - 3, (1 << 16) + 17, (1 << 19) - 1, (1 << 19) + 37):
+        got = P.lm_fwd(Gg, xd, evd[:m].contiguous()).cpu().numpy()
+        assert got.shape == (m,) and np.all(got[3:5] == 0)
+        # every length holds the first events; the last ones are its own
+        idx = np.concatenate([first, np.arange(m - 4096, m)]) if m >= 8192 else np.arange(m)
+        emax, _ = proj_err(got[idx], oracle.fwd(Go, x, ev[idx]))
+        report(f"forward split {n} tof={tof}", events=m, err=emax)
+        assert emax <= PROJ_TOL
 
 
 @pytest.mark.parametrize("n,h,tof", [
