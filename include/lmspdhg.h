@@ -90,9 +90,10 @@ const char *lm_last_error(void);
 
 /* Listmode forward projection (Eq. lmop): out[e] = (P^LM x)_e for the n
  * events ev[n][5] in the caller's order.  x: image; out: float[n].  Events
- * that are out of range get out[e] = 0.  On a cylindrical scanner (as for
- * lm_back, decided on the device) a list of at least 64 events per
- * transaxial crystal pair and fewer than 2^31 events is projected by
+ * that are out of range get out[e] = 0.  On a cylindrical scanner (crystal c
+ * of ring r at (x_c, y_c, z_r), z increasing with r; decided by a kernel that
+ * reads the crystal table) a list of at least 64 events per transaxial
+ * crystal pair and fewer than 2^31 events is projected by
  * transaxial line after a counting sort on the device: 24 more bytes per
  * event of stream-ordered temporary memory (without room for it the events
  * are projected in their own order).  The result is the same up to float32
@@ -117,13 +118,11 @@ int lm_fwd_noalloc(const lm_geom *G, const float *x, const int16_t *ev, int64_t 
 /* Listmode back projection, the adjoint of lm_fwd: img += (P^LM)^T v.  It
  * ACCUMULATES (FP32 atomics, so the summation order is not fixed); the
  * caller zeroes img.  v: float[n].  Events that are out of range or have
- * v = 0 contribute nothing.  On a cylindrical scanner (crystal c of ring r
- * at (x_c, y_c, z_r), z increasing with r) a list of at least 64 events per
- * transaxial crystal pair is back projected by transaxial line after a
- * counting sort on the device; the list then needs 32 more bytes per event
- * of stream-ordered temporary memory (without room for it the per-event
- * path runs).  Whether the scanner is cylindrical is decided by a kernel
- * that reads the crystal table: the call never synchronises the stream. */
+ * v = 0 contribute nothing.  Lists of 32768 events and more are binned by
+ * image tile on the device first, in batches that hold up to 1 GiB of
+ * segment numbers and 36 bytes per event of stream-ordered temporary memory
+ * (without room for it the per-event path runs).  The call never
+ * synchronises the stream. */
 int lm_back(const lm_geom *G, const float *v, const int16_t *ev, int64_t n, float *img,
             void *stream);
 
@@ -131,7 +130,7 @@ int lm_back(const lm_geom *G, const float *v, const int16_t *ev, int64_t n, floa
  * TOF bin (the back projection of a sinogram of ones that Algorithm 2's
  * initialisation and the step sizes T need; Section 2, after Eq.
  * lm_stepsizes).  Accumulates into g; the caller zeroes it.  On a
- * cylindrical 3D scanner (as for lm_back, decided on the device) the pairs
+ * cylindrical 3D scanner (as for lm_fwd, decided on the device) the pairs
  * are taken by transaxial line.  Asynchronous. */
 int lm_sens(const lm_geom *G, float *g, void *stream);
 

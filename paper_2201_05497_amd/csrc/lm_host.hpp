@@ -93,13 +93,6 @@ bool lines_possible(const GeomDev &g);
 int launch_cylindrical(const GeomDev &g, int *flag, hipStream_t st);
 // Sensitivity by line: nothing happens unless *cyl.
 int launch_sens_lines(const GeomDev &g, const int *cyl, float *img, hipStream_t st);
-// Lists whose back projection goes by line on a cylindrical scanner.
-bool back_by_line(const GeomDev &g, long long n);
-// Back projection of such a list by line, guarded by *cyl; `queued`
-// is false (nothing enqueued) when the list is too short or the
-// temporaries of the sort do not fit.
-int launch_back_lines(const GeomDev &g, const int *cyl, const float *v, const int16_t *ev, long long n, float *img,
-                      hipStream_t st, bool &queued);
 // For a long list (at least 64 events per transaxial crystal pair): the
 // events' indices in the order of a counting sort by transaxial crystal
 // pair (any scanner), in a stream-ordered allocation *order (nullptr: the

@@ -1,19 +1,24 @@
-// Back projection organised by transaxial line, for cylindrical scanners
-// (crystal c of ring r at (x_c, y_c, z_r)): the sensitivity image P^T 1,
-// and lm_back of long event lists after a counting sort by line.
+// The paths by transaxial line, for cylindrical scanners (crystal c of ring r
+// at (x_c, y_c, z_r)): the sensitivity image P^T 1, and lm_fwd of long event
+// lists after a counting sort by line.
 //
 // Every line of response between crystals c1 != c2 of any two rings has the
 // same transaxial projection, so when its dominant axis is transaxial it
 // meets the image planes at the same transaxial positions: only its z
-// coordinate, its length and its TOF window depend on the rings.  A
-// wavefront owns one transaxial line, 64 consecutive planes (lane l: plane
-// M0 + l) and a part of 16 z planes, and accumulates the contributions of
-// the line's LORs into LDS columns acc[corner][z][lane] (the two transaxial
-// corners of the lane's plane over the part), each lane only touching its
-// own column.  The columns are added to the image once per wavefront, so
-// the image sees one atomic per touched voxel and line instead of one per
-// LOR and voxel.  LORs whose dominant axis is z (short transaxial chords,
-// large ring differences) keep the per-LOR projector.
+// coordinate, its length and its TOF window depend on the rings.
+//
+// Sensitivity: a wavefront owns one transaxial line, 64 consecutive planes
+// (lane l: plane M0 + l) and a part of up to kZPart z planes, and accumulates
+// the contributions of the line's LORs into an LDS column acc[z][lane] over
+// the part, each lane only touching its own column.  The transaxial weights
+// of a plane are the same for every LOR of the line, so the column is split
+// over the lane's two transaxial corners only when it is added to the image,
+// once per wavefront: one atomic per touched voxel and line instead of one
+// per LOR and voxel.  Bound by instruction issue (some 25 per plane and LOR,
+// most of them in 64 bits): 384 crystals x 24 rings on 128x128x24, 13.3 -> 5.4
+// ms in all, against columns split over both transaxial corners at every LOR
+// and ring ranges found by bisection.  LORs whose dominant axis is z (short transaxial
+// chords, large ring differences) keep the per-LOR projector.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -92,99 +97,67 @@ __device__ __forceinline__ LineLane line_lane(const GeomDev &g, int c1, int c2, 
   return q;
 }
 
-// Per-LOR coefficients of a line's LOR (rings at z1, z2; TOF centre tc and
-// half-width `edge` of the weight's bin range; value v): with the lane's
-// LOR parameter lam, the TOF argument is A - lam B (units of sigma sqrt 2),
-// the bin's upper edge vh (vl = vh - D) or, for the tabulated weights, its
-// centre; the z coordinate in voxels is az + lam bz.
+// Per-LOR coefficients of a line's LOR (rings at z1, z2): with the lane's
+// LOR parameter lam, the upper edge of the TOF bins is vh = A - lam B (units
+// of sigma sqrt 2; all bins together: centre 0, half-width `edge`), the z
+// coordinate in voxels is az + lam bz, and c is the value of a sample before
+// its TOF weight.
 struct Lor {
   double A, B, az, bz;
-  float D, c;  // c = v L
+  float c;
 };
 
-// The z coefficients first (cheap, they decide whether the LOR touches a
-// wavefront's z part), then the rest.
-__device__ __forceinline__ void lor_z(const GeomDev &g, double ihz, double z1, double z2, Lor &o) {
+__device__ __forceinline__ Lor line_lor_sum(const GeomDev &g, const LineLane &q, double ihz, double z1, double z2,
+                                            double edge) {
+  Lor o;
   o.az = (z1 - g.c0[2]) * ihz;
   o.bz = (z2 - z1) * ihz;
-}
-
-__device__ __forceinline__ void lor_rest(const GeomDev &g, const LineLane &q, double z1, double z2, double tc,
-                                         double edge, bool centred, float v, Lor &o) {
   const double dz = z2 - z1;
   const double dn = sqrt(q.dxy2 + dz * dz);
-  // t(lam) = (lam - 1/2) dn, vh = (tc + edge - t) / (sigma sqrt 2)
-  o.A = (tc + (centred ? 0.0 : edge) + 0.5 * dn) * g.inv_sr2;
+  // t(lam) = (lam - 1/2) dn, vh = (edge - t) / (sigma sqrt 2)
+  o.A = (edge + 0.5 * dn) * g.inv_sr2;
   o.B = dn * g.inv_sr2;
-  o.D = (float)(2.0 * edge * g.inv_sr2);
-  o.c = v * (float)(q.ha_over_da * dn);
+  o.c = (float)(q.ha_over_da * dn);
+  return o;
 }
 
-// A wavefront's share of the columns: z in [zlo, zlo + zc), acc[cb][z - zlo][lane].
+// A wavefront's columns: rows -1 .. zc of z planes zlo - 1 .. zlo + zc (the
+// first and the last take what belongs to the neighbouring parts, or to
+// nobody, and are thrown away), acc[z - zlo + 1][lane].
 struct ZPart {
   int zlo, zc;
 };
 
-// Adds one LOR's samples at the lane's plane to the lane's column.  With a
-// TOF table (single bins) the weight is read from it; otherwise wfull is the
-// weight of a sample whose TOF argument covers the whole truncated Gaussian
-// (vh >= vclip and vl <= -vclip), the same value tof_weight gives for it, so
-// that such samples skip the two erfc evaluations.
-template <bool TAB>
-__device__ __forceinline__ void add_lor(const GeomDev &g, const LineLane &q, const Lor &o, const ZPart &zp,
-                                        float wfull, const TofTab &tt, const float4 *tab, float *acc, int nz,
-                                        int lane) {
-  if (!q.active) return;
-  float c = o.c;
-  if (g.tof_on) {
-    const float vh = (float)fma(-q.lam, o.B, o.A);  // with TAB: the centre
-    if constexpr (TAB) {
-      c *= tof_weight_tab(tt, tab, vh);
-    } else {
-      const float vl = vh - o.D;
-      c *= (vh >= g.vclip && vl <= -g.vclip) ? wfull : tof_weight(vh, vl, g.vclip, g.inv_norm);
-    }
-  }
-  if (c == 0.0f) return;
-  const double u2 = fma(q.lam, o.bz, o.az);
+// Adds a sample of value c at LOR parameter lam to the lane's column: its
+// two z corners (no other lane or wavefront touches the column).
+__device__ __forceinline__ void add_column(const Lor &o, double lam, float c, const ZPart &zp, float *col) {
+  const double u2 = fma(lam, o.bz, o.az);
   const double fl = floor(u2);
-  if (fl < -1.0 || fl > (double)nz - 1.0) return;
-  const int k0 = (int)fl;
+  const int row = (int)fl - zp.zlo + 1;
   const float f2 = (float)(u2 - fl);
-  // the four corners are distinct entries of the lane's own column (no
-  // other lane or wavefront touches it): all reads first, then all writes,
-  // so that their LDS latencies overlap
-  bool ok[4];
-  float *ad[4];
-  float w[4], old[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int cb = t >> 1, cz = t & 1;
-    const int kz = k0 + cz - zp.zlo;
-    ok[t] = (unsigned)(q.i1 + cb) < (unsigned)q.nb && (unsigned)kz < (unsigned)zp.zc && k0 + cz < nz;
-    ad[t] = acc + ((cb * zp.zc + (ok[t] ? kz : 0)) * kLanes + lane);
-    w[t] = c * (cb ? q.f1 : 1.0f - q.f1) * (cz ? f2 : 1.0f - f2);
+  if ((unsigned)row <= (unsigned)zp.zc) {
+    float *p = col + row * kLanes;
+    const float o0 = p[0], o1 = p[kLanes];
+    p[0] = fmaf(c, 1.0f - f2, o0);
+    p[kLanes] = fmaf(c, f2, o1);
   }
-#pragma unroll
-  for (int t = 0; t < 4; ++t) old[t] = ok[t] ? *ad[t] : 0.0f;
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-    if (ok[t]) *ad[t] = old[t] + w[t];
 }
 
-// Adds the lane's columns to the image: one atomic per non-zero voxel.
-__device__ __forceinline__ void flush(const GeomDev &g, const LineLane &q, const ZPart &zp, const float *acc,
-                                      float *img, int lane) {
+// Adds the lane's column to the image, split over its two transaxial
+// corners: one atomic per non-zero voxel.
+__device__ __forceinline__ void flush(const GeomDev &g, const LineLane &q, const ZPart &zp, const float *col,
+                                      float *img) {
   const Layout &L = g.lay;
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) {
     const int ib = q.i1 + cb;
-    const bool ok = q.active && (unsigned)ib < (unsigned)q.nb;
+    const float w = cb ? q.f1 : 1.0f - q.f1;
+    if (!q.active || (unsigned)ib >= (unsigned)q.nb || w == 0.0f) continue;
     const int i = q.a == 0 ? q.m : ib, j = q.a == 0 ? ib : q.m;
-    const int base = ok ? vidx(L, i, j, 0) : 0;
+    const int base = vidx(L, i, j, 0);
     for (int kz = 0; kz < zp.zc; ++kz) {
-      const float v = acc[(cb * zp.zc + kz) * kLanes + lane];
-      if (ok && v != 0.0f) atomicAdd(img + (base + vidx(L, 0, 0, zp.zlo + kz)), v);
+      const float v = w * col[(kz + 1) * kLanes];
+      if (v != 0.0f) atomicAdd(img + (base + vidx(L, 0, 0, zp.zlo + kz)), v);
     }
   }
 }
@@ -196,34 +169,30 @@ __device__ __forceinline__ double readlane_f64(double x, int j) {
   const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), j);
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
-
-// Lane j's LOR coefficients (j uniform).
-__device__ __forceinline__ Lor broadcast(const Lor &o, int j) {
-  Lor r;
-  r.A = readlane_f64(o.A, j);
-  r.B = readlane_f64(o.B, j);
-  r.az = readlane_f64(o.az, j);
-  r.bz = readlane_f64(o.bz, j);
-  r.D = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(o.D), j));
-  r.c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(o.c), j));
-  return r;
+__device__ __forceinline__ float readlane_f32(float x, int j) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), j));
 }
 
-// z extent of a part: 2 x kZPart x 64 floats (8 KB) of LDS per wavefront,
-// which allows 20 wavefronts per CU.  Measured on 5e8 events: parts of 8,
-// 12, 16 and 32 planes took 439, 638, 364 and 438 ms (smaller parts test
-// and add each event in more blocks, larger ones leave fewer wavefronts to
-// hide the latency of each event's LDS updates).
-constexpr int kZPart = 16;
+// z extent of a part: kZPart + 2 rows of 64 floats (8.7 KB) of LDS per
+// wavefront, which with the rings allows 16 wavefronts per CU.
+constexpr int kZPart = 32;
+// Rings whose z positions a wavefront keeps in LDS (those beyond are read
+// from the crystal table).
+constexpr int kLdsRings = 256;
 
 // Sensitivity over the LORs of every line c1 < c2 whose dominant axis is
 // transaxial: all ring pairs (r1, r2), the TOF weight summed over all bins.
 // Block b (one wavefront): line b / (nchunk nzp), planes 64 chunk .. + 63
-// with chunk = (b / nzp) % nchunk, and z part b % nzp.  A LOR whose z range
-// over the chunk's planes misses the part is skipped on uniform values.
+// with chunk = (b / nzp) % nchunk, and z part b % nzp.  64 ring pairs (r1,
+// r2) at a time, lane l sets up and tests pair r2 = b + l, then the wavefront
+// adds those that reach the part one after the other, their coefficients
+// broadcast.  Where the bins cover the whole truncated Gaussian at both ends
+// of the chunk (the scanner's bins reach beyond its bore) every sample's
+// weight is the same, and the pair is added without TOF arithmetic.
 __global__ __launch_bounds__(kLanes) void k_sens_lines(GeomDev g, const int *cyl, long long p0, long long nlines,
                                                        int nchunk, int nzp, float *img) {
-  __shared__ float acc[2 * kZPart * kLanes];
+  extern __shared__ float acc[];  // (min(kZPart, nz) + 2) * kLanes
+  __shared__ float ring_z[kLdsRings];
   if (!*cyl) return;
   const long long blk = (long long)blockIdx.x;
   const long long per_line = (long long)nchunk * nzp;
@@ -231,10 +200,9 @@ __global__ __launch_bounds__(kLanes) void k_sens_lines(GeomDev g, const int *cyl
   const long long p = p0 + blk / per_line;
   const int chunk = (int)((blk / nzp) % nchunk), part = (int)(blk % nzp);
   const int lane = threadIdx.x;
-  const int nz = g.n[2];
   ZPart zp;
   zp.zlo = part * kZPart;
-  zp.zc = min(kZPart, nz - zp.zlo);
+  zp.zc = min(kZPart, g.n[2] - zp.zlo);
   int c1, c2;
   pair_of(p, g.n_cry, c1, c2);
   const LineLane q = line_lane(g, c1, c2, chunk * kLanes, lane);
@@ -243,73 +211,67 @@ __global__ __launch_bounds__(kLanes) void k_sens_lines(GeomDev g, const int *cyl
   // LOR parameter at the first and last active plane of the chunk
   const int la = __ffsll((long long)act) - 1, lb = 63 - __clzll((long long)act);
   const double lam_a = __shfl(q.lam, la), lam_b = __shfl(q.lam, lb);
-  for (int i = lane; i < 2 * zp.zc * kLanes; i += kLanes) acc[i] = 0.0f;
-  const double edge = (g.kmax + 0.5) * g.tof_bin;  // all bins: centre 0
-  const float wfull = tof_weight(g.vclip, -g.vclip, g.vclip, g.inv_norm);
+  for (int i = lane; i < (zp.zc + 2) * kLanes; i += kLanes) acc[i] = 0.0f;
   const int nr = g.n_ring;
+  auto ring_from_table = [&](int r) { return g.det[3 * ((long long)g.n_cry * r) + 2]; };
+  for (int r = lane; r < min(nr, kLdsRings); r += kLanes) ring_z[r] = ring_from_table(r);
+  __syncthreads();
+  auto zring = [&](int r) { return r < kLdsRings ? ring_z[r] : ring_from_table(r); };
+  const double edge = (g.kmax + 0.5) * g.tof_bin;  // all bins: centre 0
+  const double D = 2.0 * edge * g.inv_sr2;
+  const float Df = (float)D;
+  const float wfull = g.tof_on ? tof_weight(g.vclip, -g.vclip, g.vclip, g.inv_norm) : 1.0f;
   const double ihz = 1.0 / g.h[2];
-  auto zring = [&](int r) { return g.det[3 * (g.n_cry * r) + 2]; };
+  float *col = acc + lane;
   for (int r1 = 0; r1 < nr; ++r1) {
     const float z1f = zring(r1);
-    // The LOR (r1, r2) can touch the part when its corners over the chunk,
-    // floor(u) - 1 .. floor(u) + 2 for u between ua and ub (one voxel of
-    // margin on each side for rounding between the end planes), reach
-    // [zlo, zlo + zc).  With z increasing with the ring (checked on the
-    // host) both bounds grow with r2, so those r2 form one interval, found
-    // by bisection on the same expressions.
-    auto u_ends = [&](int r2, double &umin, double &umax) {
-      Lor o;
-      lor_z(g, ihz, z1f, zring(r2), o);
-      const double ua = fma(lam_a, o.bz, o.az), ub = fma(lam_b, o.bz, o.az);
-      umin = fmin(ua, ub);
-      umax = fmax(ua, ub);
-    };
-    auto reaches_lo = [&](int r2) {  // floor(umax) + 2 >= zlo
-      double umin, umax;
-      u_ends(r2, umin, umax);
-      return floor(umax) + 2.0 >= (double)zp.zlo;
-    };
-    auto below_hi = [&](int r2) {  // floor(umin) - 1 < zlo + zc
-      double umin, umax;
-      u_ends(r2, umin, umax);
-      return floor(umin) - 1.0 < (double)(zp.zlo + zp.zc);
-    };
-    int lo = 0, hi = nr;  // first r2 with reaches_lo
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (reaches_lo(mid)) hi = mid; else lo = mid + 1;
-    }
-    const int r2a = lo;
-    lo = r2a;
-    hi = nr;  // first r2 >= r2a without below_hi
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (below_hi(mid)) lo = mid + 1; else hi = mid;
-    }
-    const int r2b = lo;
-    // 64 ring pairs at a time: lane l sets up ring pair r2 = b + l, then
-    // the wavefront adds them one after the other
-    for (int b = r2a; b < r2b; b += kLanes) {
+    for (int b = 0; b < nr; b += kLanes) {
       const int r2 = b + lane;
-      bool pass = false;
-      Lor o;
-      o.A = o.B = o.az = o.bz = 0.0;
-      o.D = o.c = 0.0f;
-      if (r2 < r2b) {
+      bool pass = false, full = true;
+      Lor o{};
+      if (r2 < nr) {
         const float z2f = zring(r2);
-        pass = dominant_axis(q.fdx, q.fdy, z2f - z1f) != 2;  // z dominant: per-LOR path
-        lor_z(g, ihz, z1f, z2f, o);
-        lor_rest(g, q, z1f, z2f, 0.0, edge, false, 1.0f, o);
+        o = line_lor_sum(g, q, ihz, z1f, z2f, edge);
+        const double ua = fma(lam_a, o.bz, o.az), ub = fma(lam_b, o.bz, o.az);
+        // z dominant: per-LOR path; z range over the chunk inside the part
+        // (one voxel of margin on each side for rounding between the ends)
+        pass = dominant_axis(q.fdx, q.fdy, z2f - z1f) != 2 && floor(fmax(ua, ub)) + 2.0 >= (double)zp.zlo &&
+               floor(fmin(ua, ub)) - 1.0 < (double)(zp.zlo + zp.zc);
+        if (g.tof_on) {
+          const double va = fma(-lam_a, o.B, o.A), vb = fma(-lam_b, o.B, o.A);
+          full = fmin(va, vb) >= g.vclip + 1e-3 && fmax(va, vb) - D <= -g.vclip - 1e-3;
+        }
+        if (full) o.c *= wfull;
       }
-      unsigned long long m = __ballot(pass);
-      while (m) {
-        const int j = __ffsll((long long)m) - 1;
-        m &= m - 1;
-        add_lor<false>(g, q, broadcast(o, j), zp, wfull, TofTab{}, nullptr, acc, nz, lane);
+      unsigned long long mf = __ballot(pass && full), mp = __ballot(pass && !full);
+      while (mf) {
+        const int j = __ffsll((long long)mf) - 1;
+        mf &= mf - 1;
+        Lor u;
+        u.az = readlane_f64(o.az, j);
+        u.bz = readlane_f64(o.bz, j);
+        u.c = readlane_f32(o.c, j);
+        if (q.active) add_column(u, q.lam, u.c, zp, col);
+      }
+      while (mp) {
+        const int j = __ffsll((long long)mp) - 1;
+        mp &= mp - 1;
+        Lor u;
+        u.A = readlane_f64(o.A, j);
+        u.B = readlane_f64(o.B, j);
+        u.az = readlane_f64(o.az, j);
+        u.bz = readlane_f64(o.bz, j);
+        u.c = readlane_f32(o.c, j);
+        if (q.active) {
+          const float vh = (float)fma(-q.lam, u.B, u.A), vl = vh - Df;
+          const float c = u.c * ((vh >= g.vclip && vl <= -g.vclip) ? wfull
+                                                                  : tof_weight(vh, vl, g.vclip, g.inv_norm));
+          add_column(u, q.lam, c, zp, col);
+        }
       }
     }
   }
-  flush(g, q, zp, acc, img, lane);
+  flush(g, q, zp, col, img);
 }
 
 // Stage for the per-LOR scatter (one wavefront per block).
@@ -365,167 +327,6 @@ __global__ __launch_bounds__(kLanes) void k_sens_zdom(GeomDev g, const int *cyl,
 
 
 // ---------------------------------------------------------------------------
-// Back projection of a long event list by line: the events are counted and
-// placed per line (a counting sort on the GPU), then one wavefront per
-// (line, chunk, z part) accumulates its line's events as the sensitivity
-// kernel does its ring pairs.  Events whose dominant axis is z take the
-// per-event projector.
-
-// An event on a line in the line's orientation (crystal c1 < c2): rings and
-// TOF bin packed as r1 | r2 << 12 | (k + kmax) << 24, and its value.
-struct LineRec {
-  unsigned rk;
-  float v;
-};
-
-// Line of a caller event; kPerEvent for an event the per-event projector
-// takes (a z dominant axis, which includes both ends on one transaxial
-// crystal), kNoEvent for one that contributes nothing (out of range, zero
-// value, the same crystal twice).  rk as in LineRec.
-constexpr int kNoEvent = -1, kPerEvent = -2;
-
-__device__ __forceinline__ int event_line(const GeomDev &g, const int16_t *e, float v, unsigned &rk) {
-  int id1, id2, k;
-  if (!decode_event(g, e, id1, id2, k) || v == 0.0f) return kNoEvent;
-  int c1 = e[0], r1 = e[1], c2 = e[2], r2 = e[3];
-  if (c1 == c2) return r1 == r2 ? kNoEvent : kPerEvent;
-  if (c1 > c2) {  // the line's orientation: swap the ends, mirror the TOF bin
-    const int tc = c1, tr = r1;
-    c1 = c2;
-    r1 = r2;
-    c2 = tc;
-    r2 = tr;
-    k = -k;
-  }
-  const float *d1 = g.det + 3 * c1, *d2 = g.det + 3 * c2;
-  const float dz = g.det[3 * (g.n_cry * r2) + 2] - g.det[3 * (g.n_cry * r1) + 2];
-  if (dominant_axis(d2[0] - d1[0], d2[1] - d1[1], dz) == 2) return kPerEvent;
-  rk = (unsigned)r1 | ((unsigned)r2 << 12) | ((unsigned)(k + g.kmax) << 24);
-  const long long n = g.n_cry;
-  return (int)(c1 * n - (long long)c1 * (c1 + 1) / 2 + (c2 - c1 - 1));
-}
-
-// Line of every event (negative: not by line) and its record.
-__global__ __launch_bounds__(256) void k_line_keys(GeomDev g, const int *cyl, const int16_t *ev, const float *v,
-                                                   long long n, int *key, LineRec *rec) {
-  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= n || !*cyl) return;
-  unsigned rk;
-  const int L = event_line(g, ev + 5 * e, v[e], rk);
-  key[e] = L;
-  LineRec r;
-  r.rk = rk;
-  r.v = v[e];
-  rec[e] = r;
-}
-
-// Back projection of the events of every line (records rec[off[L] ..
-// off[L+1])); blocks as in k_sens_lines.  An event is skipped on uniform
-// values when its TOF window or its z range misses the chunk and part.
-__global__ __launch_bounds__(kLanes) void k_back_lines(GeomDev g, const int *cyl, const unsigned *off,
-                                                       const LineRec *rec, long long p0, long long nlines, int nchunk,
-                                                       int nzp, TofTab tt, const float4 *tab, float *img) {
-  __shared__ float acc[2 * kZPart * kLanes];
-  if (!*cyl) return;
-  const long long blk = (long long)blockIdx.x;
-  const long long per_line = (long long)nchunk * nzp;
-  if (blk / per_line >= nlines) return;
-  const long long p = p0 + blk / per_line;
-  const unsigned e0 = off[p], e1 = off[p + 1];
-  if (e0 == e1) return;
-  const int chunk = (int)((blk / nzp) % nchunk), part = (int)(blk % nzp);
-  const int lane = threadIdx.x;
-  const int nz = g.n[2];
-  ZPart zp;
-  zp.zlo = part * kZPart;
-  zp.zc = min(kZPart, nz - zp.zlo);
-  int c1, c2;
-  pair_of(p, g.n_cry, c1, c2);
-  const LineLane q = line_lane(g, c1, c2, chunk * kLanes, lane);
-  const unsigned long long act = __ballot(q.active);
-  if (act == 0) return;
-  const int la = __ffsll((long long)act) - 1, lb = 63 - __clzll((long long)act);
-  const double lam_a = __shfl(q.lam, la), lam_b = __shfl(q.lam, lb);
-  for (int i = lane; i < 2 * zp.zc * kLanes; i += kLanes) acc[i] = 0.0f;
-  const double edge = 0.5 * g.tof_bin;
-  const float wfull = tof_weight(g.vclip, -g.vclip, g.vclip, g.inv_norm);
-  const TofTab tu = tof_tab_uniform(tt);
-  const double ihz = 1.0 / g.h[2];
-  // 64 events at a time: each lane loads one event and tests it (z range,
-  // TOF window) for this chunk and part, then the wavefront adds the events
-  // that pass, one after the other, with their coefficients broadcast.
-  for (unsigned b0 = e0; b0 < e1; b0 += kLanes) {
-    const unsigned e = b0 + lane;
-    bool pass = false;
-    Lor o;
-    o.A = o.B = o.az = o.bz = 0.0;
-    o.D = o.c = 0.0f;
-    if (e < e1) {
-      const LineRec r = rec[e];
-      const int r1 = (int)(r.rk & 4095u), r2 = (int)((r.rk >> 12) & 4095u), k = (int)(r.rk >> 24) - g.kmax;
-      const float z1f = g.det[3 * (g.n_cry * r1) + 2], z2f = g.det[3 * (g.n_cry * r2) + 2];
-      lor_z(g, ihz, z1f, z2f, o);
-      const double ua = fma(lam_a, o.bz, o.az), ub = fma(lam_b, o.bz, o.az);
-      // z range inside the part (one voxel of margin)
-      pass = !(floor(fmax(ua, ub)) + 2.0 < (double)zp.zlo ||
-               floor(fmin(ua, ub)) - 1.0 >= (double)(zp.zlo + zp.zc));
-      if (pass) {
-        lor_rest(g, q, z1f, z2f, k * g.tof_bin, edge, tab != nullptr, r.v, o);
-        if (g.tof_on) {
-          // vh decreases along the line: every sample of the chunk lies
-          // beyond one edge of the bin's truncated window (a margin for
-          // rounding)
-          const double up = tab ? edge * g.inv_sr2 : 0.0;  // from the centre to the upper edge
-          const double vh_a = o.A + up - lam_a * o.B, vh_b = o.A + up - lam_b * o.B;
-          if (fmin(vh_a, vh_b) - o.D >= g.vclip + 1e-3 || fmax(vh_a, vh_b) <= -g.vclip - 1e-3) pass = false;
-        }
-      }
-    }
-    unsigned long long m = __ballot(pass);
-    while (m) {
-      const int j = __ffsll((long long)m) - 1;
-      m &= m - 1;
-      if (tab)
-        add_lor<true>(g, q, broadcast(o, j), zp, wfull, tu, tab, acc, nz, lane);
-      else
-        add_lor<false>(g, q, broadcast(o, j), zp, wfull, tu, tab, acc, nz, lane);
-    }
-  }
-  flush(g, q, zp, acc, img, lane);
-}
-
-// The events the line pass leaves to the per-event projector (key
-// kPerEvent).  Each wavefront reads the keys of 64 events at a time and
-// projects the marked ones one after the other (a whole wavefront per
-// event, as the plain back projection); the grid strides over the list.
-__global__ __launch_bounds__(256) void k_back_zdom(GeomDev g, const int *cyl, const float *v, const int16_t *ev,
-                                                   const int *key, long long n, float *img) {
-  __shared__ Stage1 st[4];
-  if (!*cyl) return;
-  const int lane = threadIdx.x % kLanes, wv = threadIdx.x / kLanes;
-  const long long nw = (long long)gridDim.x * 4;
-  for (long long b0 = ((long long)blockIdx.x * 4 + wv) * kLanes; b0 < n; b0 += nw * kLanes) {
-    const long long e = b0 + lane;
-    unsigned long long m = __ballot(e < n && key[e] == kPerEvent);
-    while (m) {
-      const int jl = __ffsll((long long)m) - 1;
-      m &= m - 1;
-      const long long ej = b0 + jl;
-      int id1, id2, k;
-      decode_event(g, ev + 5 * ej, id1, id2, k);  // valid: the key is set only for valid events
-      const Ray r = setup_ray(g, id1, id2, k, W_BIN, 1 << 20);
-      const float c = r.L * v[ej];
-      const int o = brick_offset(g.lay, r);
-      for (int j0 = -o; j0 < r.nplanes; j0 += kLanes) {
-        const int j = j0 + lane;
-        Sample s = sample_at(g, r, j, g.tof_on);
-        const float cs = (j >= 0 && j < r.nplanes) ? c * s.w : 0.0f;
-        scatter_interleaved(g, img, r, s, cs, lane, st[wv].idx, st[wv].val);
-      }
-    }
-  }
-}
-
 // The order of lm_fwd for a long list: the bucket of every event (its
 // transaxial crystal pair c1 != c2 as line index; events of one crystal or
 // out of range in bucket nlines), grouped by group_by_key.
@@ -908,13 +709,14 @@ __global__ __launch_bounds__(256) void k_tof_table(TofTab t, double vc, double D
 // increasing in r.  One block checks every crystal and writes flag[0] = 1
 // (cylindrical) or 0; the kernels of the two paths read the flag, so the
 // decision never waits for the host.
-__global__ __launch_bounds__(256) void k_cylindrical(GeomDev g, int *flag) {
+__global__ __launch_bounds__(1024) void k_cylindrical(GeomDev g, int *flag) {
   __shared__ int bad;
   if (threadIdx.x == 0) bad = 0;
   __syncthreads();
   int b = 0;
   const float *d = g.det;
-  for (int i = threadIdx.x; i < g.n_det; i += 256) {
+#pragma unroll 4
+  for (int i = threadIdx.x; i < g.n_det; i += 1024) {
     const int r = i / g.n_cry, c = i - r * g.n_cry;
     const float *p = d + 3 * (long long)i;
     if (p[0] != d[3 * c] || p[1] != d[3 * c + 1] || p[2] != d[3 * (long long)g.n_cry * r + 2]) b = 1;
@@ -932,7 +734,7 @@ namespace lmk {
 bool lines_possible(const GeomDev &g) { return g.n_ring >= 2 && g.n_cry >= 2; }
 
 int launch_cylindrical(const GeomDev &g, int *flag, hipStream_t st) {
-  hipLaunchKernelGGL(k_cylindrical, dim3(1), dim3(256), 0, st, g, flag);
+  hipLaunchKernelGGL(k_cylindrical, dim3(1), dim3(1024), 0, st, g, flag);
   LM_TRY_HIP(hipGetLastError());
   return LM_OK;
 }
@@ -942,13 +744,14 @@ int launch_sens_lines(const GeomDev &g, const int *cyl, float *img, hipStream_t 
   const int na_max = std::max(g.n[0], g.n[1]);
   const int nchunk = (na_max + kLanes - 1) / kLanes;
   const int nzp = (g.n[2] + kZPart - 1) / kZPart;
+  const size_t lds = (size_t)(std::min(kZPart, g.n[2]) + 2) * kLanes * sizeof(float);
   const long long nlines = (long long)g.n_cry * (g.n_cry - 1) / 2;
   // at most 2^24 blocks of 64 work-items per launch
   const long long per = std::max<long long>(1, (1LL << 24) / ((long long)nchunk * nzp));
   for (long long p0 = 0; p0 < nlines; p0 += per) {
     const long long m = std::min(per, nlines - p0);
-    hipLaunchKernelGGL(k_sens_lines, dim3((unsigned)(m * nchunk * nzp)), dim3(kLanes), 0, st, g, cyl, p0, m, nchunk,
-                       nzp, img);
+    hipLaunchKernelGGL(k_sens_lines, dim3((unsigned)(m * nchunk * nzp)), dim3(kLanes), lds, st, g, cyl, p0, m,
+                       nchunk, nzp, img);
     LM_TRY_HIP(hipGetLastError());
   }
   const long long npz = (long long)g.n_cry * (g.n_cry + 1) / 2;  // c1 <= c2
@@ -989,7 +792,7 @@ int sort_events_by_line(const GeomDev &g, const int16_t *ev, long long n, unsign
     release(false);
     LM_TRY_HIP(e);
   }
-  const int rc = group_by_key(key, (const unsigned *)nullptr, n, (unsigned)(nlines + 1), nullptr, ord, off, st);
+  const int rc = group_by_key(key, n, (unsigned)(nlines + 1), ord, off, st);
   if (rc == LM_ENOMEM) {
     release(false);
     lmh::clear_error();
@@ -1072,93 +875,6 @@ int launch_fwd_lines(const GeomDev &g, const int *cyl, const float *x, const int
   const hipError_t e = hipGetLastError();
   if (tab) (void)hipFreeAsync(tab, st);  // release errors have no caller to go to
   (void)hipFreeAsync(rec, st);
-  LM_TRY_HIP(e);
-  queued = true;
-  return LM_OK;
-}
-
-// Back projection of a long list by line: worth it when the lines carry
-// many events each (the per-block flush costs about as many atomics as
-// a few tens of events do on the per-event path).
-constexpr long long kMinEventsPerLine = 64;
-
-bool back_by_line(const GeomDev &g, long long n) {
-  const long long nlines = (long long)g.n_cry * (g.n_cry - 1) / 2;
-  // the records hold rings in 12 bits and the TOF bin in 8
-  if (!lines_possible(g) || g.n_ring > 4096 || g.n_tof > 255) return false;
-  return n >= kMinEventsPerLine * nlines && n < (1LL << 31) && nlines <= (long long)kGroupMaxBuckets;
-}
-
-int launch_back_lines(const GeomDev &g, const int *cyl, const float *v, const int16_t *ev, long long n, float *img,
-                      hipStream_t st, bool &queued) {
-  queued = false;
-  const long long nlines = (long long)g.n_cry * (g.n_cry - 1) / 2;
-  if (!back_by_line(g, n)) return LM_OK;
-  int *key = nullptr;
-  unsigned *off = nullptr;
-  LineRec *rec = nullptr, *recu = nullptr;
-  auto release = [&]() {  // release errors are not reported
-    if (key) (void)hipFreeAsync(key, st);
-    if (off) (void)hipFreeAsync(off, st);
-    if (rec) (void)hipFreeAsync(rec, st);
-    if (recu) (void)hipFreeAsync(recu, st);
-  };
-  hipError_t e = hipMallocAsync((void **)&key, n * sizeof(int), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&off, (nlines + 1) * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&rec, n * sizeof(LineRec), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&recu, n * sizeof(LineRec), st);
-  if (e == hipErrorOutOfMemory) {
-    // no room for the sort: the per-event path needs no temporaries
-    release();
-    (void)hipGetLastError();
-    return LM_OK;
-  }
-  const unsigned grid = (unsigned)((n + 255) / 256);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_line_keys, dim3(grid), dim3(256), 0, st, g, cyl, ev, v, n, key, recu);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess) {
-    // events of no line (negative keys) are dropped from the records
-    static_assert(sizeof(LineRec) == sizeof(unsigned long long), "a record is one 64-bit payload");
-    const int rc = group_by_key((const unsigned *)key, (const unsigned long long *)recu, n, (unsigned)nlines, cyl,
-                                (unsigned long long *)rec, off, st);
-    if (rc == LM_ENOMEM) {
-      release();
-      lmh::clear_error();
-      return LM_OK;  // the per-event path
-    }
-    if (rc != LM_OK) {
-      release();
-      return rc;
-    }
-  }
-  const int na_max = std::max(g.n[0], g.n[1]);
-  const int nchunk = (na_max + kLanes - 1) / kLanes;
-  const int nzp = (g.n[2] + kZPart - 1) / kZPart;
-  const long long per = std::max<long long>(1, (1LL << 24) / ((long long)nchunk * nzp));
-  TofTab tt{};
-  float4 *tab = nullptr;
-  if (e == hipSuccess) {
-    if (int rc = build_tof_table(g, tt, &tab, st)) {
-      release();
-      return rc;
-    }
-  }
-  for (long long p0 = 0; e == hipSuccess && p0 < nlines; p0 += per) {
-    const long long m = std::min(per, nlines - p0);
-    hipLaunchKernelGGL(k_back_lines, dim3((unsigned)(m * nchunk * nzp)), dim3(kLanes), 0, st, g, cyl, off, rec, p0,
-                       m, nchunk, nzp, tt, tab, img);
-    e = hipGetLastError();
-  }
-  if (tab) (void)hipFreeAsync(tab, st);  // a release error has no caller to go to
-  if (e == hipSuccess) {
-    // 4096 blocks of 4 wavefronts stride over the list
-    const long long nb = std::min<long long>(4096, (n + 4 * kLanes - 1) / (4 * kLanes));
-    hipLaunchKernelGGL(k_back_zdom, dim3((unsigned)nb), dim3(256), 0, st, g, cyl, v, ev, key, n, img);
-    e = hipGetLastError();
-  }
-  release();
   LM_TRY_HIP(e);
   queued = true;
   return LM_OK;

@@ -132,15 +132,12 @@ struct Stage {
   float val[kBlock / 64][256];
 };
 
-// Back projection: one event per wavefront, the scatter of every 64 planes
-// interleaved over corners; the grid strides over the list.  With `skip`
-// set the kernel does nothing when *skip is non-zero (the list went to the
-// transaxial-line path instead).
+// Back projection of a short list: one event per wavefront, the scatter of
+// every 64 planes interleaved over corners; the grid strides over the list.
 template <class Src>
-__global__ __launch_bounds__(kBlock) void k_back(GeomDev g, const int *skip, const float *__restrict__ v, Src src,
-                                                 long long n, float *img) {
+__global__ __launch_bounds__(kBlock) void k_back(GeomDev g, const float *__restrict__ v, Src src, long long n,
+                                                 float *img) {
   __shared__ Stage st;
-  if (skip && *skip) return;
   const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
   const long long stride = (long long)gridDim.x * (kBlock / 64);
   for (long long e = (long long)blockIdx.x * (kBlock / 64) + wv; e < n; e += stride) {
@@ -367,16 +364,14 @@ static int fwd_impl(const GeomDev &g, const float *x, Src src, long long n, floa
 }
 
 // Grid of the grid-stride scattering kernels: enough wavefronts to fill the
-// chip many times over, few enough that a launch whose work went to another
-// path costs next to nothing.
-constexpr long long kStrideBlocks = 1LL << 16;
+// chip, few enough that a launch whose work went to another path costs next
+// to nothing (65536 blocks that return at once took 15 us, 4096 take 2).
+constexpr long long kStrideBlocks = 1LL << 12;
 
 template <class Src>
-static int back_impl(const GeomDev &g, const int *skip, const float *v, Src src, long long n, float *img,
-                     hipStream_t st) {
-  if (n == 0) return LM_OK;
+static int back_impl(const GeomDev &g, const float *v, Src src, long long n, float *img, hipStream_t st) {
   const long long nb = std::min<long long>(kStrideBlocks, blocks_for(n, 64));
-  hipLaunchKernelGGL((k_back<Src>), dim3((unsigned)nb), dim3(kBlock), 0, st, g, skip, v, src, n, img);
+  hipLaunchKernelGGL((k_back<Src>), dim3((unsigned)nb), dim3(kBlock), 0, st, g, v, src, n, img);
   LM_TRY_HIP(hipGetLastError());
   return LM_OK;
 }
@@ -403,29 +398,24 @@ struct DevFlag {
 int launch_fwd(const GeomDev &g, const float *x, const int16_t *ev, long long n, float *out, hipStream_t st) {
   return fwd_impl(g, x, CallerEvents{ev}, n, out, st);
 }
-int launch_back(const GeomDev &g, const float *v, const int16_t *ev, long long n, float *img, hipStream_t st) {
+// By tile, or per event where the list is short or the tile path does not
+// apply.
+static int back_any(const GeomDev &g, const float *v, const int16_t *ev, const int4 *rec, long long n, float *img,
+                    hipStream_t st) {
   if (n == 0) return LM_OK;
   bool queued = false;
-  if (back_by_line(g, n)) {
-    DevFlag cyl;
-    if (int rc = cyl.alloc(st)) return rc;
-    if (int rc = launch_cylindrical(g, cyl.p, st)) return rc;
-    if (int rc = launch_back_lines(g, cyl.p, v, ev, n, img, st, queued)) return rc;
-    // queued on a scanner that is not cylindrical: the per-event kernel
-    // takes the list
-    if (queued) return back_impl(g, cyl.p, v, CallerEvents{ev}, n, img, st);
-  }
-  if (int rc = launch_back_tiles(g, v, ev, nullptr, n, img, st, queued)) return rc;
-  return queued ? LM_OK : back_impl(g, nullptr, v, CallerEvents{ev}, n, img, st);
+  if (int rc = launch_back_tiles(g, v, ev, rec, n, img, st, queued)) return rc;
+  if (queued) return LM_OK;
+  return ev ? back_impl(g, v, CallerEvents{ev}, n, img, st) : back_impl(g, v, PlanEvents{rec}, n, img, st);
+}
+int launch_back(const GeomDev &g, const float *v, const int16_t *ev, long long n, float *img, hipStream_t st) {
+  return back_any(g, v, ev, nullptr, n, img, st);
 }
 int launch_fwd_rec(const GeomDev &g, const float *x, const int4 *rec, long long n, float *out, hipStream_t st) {
   return fwd_impl(g, x, PlanEvents{rec}, n, out, st);
 }
 int launch_back_rec(const GeomDev &g, const float *v, const int4 *rec, long long n, float *img, hipStream_t st) {
-  if (n == 0) return LM_OK;
-  bool queued = false;
-  if (int rc = launch_back_tiles(g, v, nullptr, rec, n, img, st, queued)) return rc;
-  return queued ? LM_OK : back_impl(g, nullptr, v, PlanEvents{rec}, n, img, st);
+  return back_any(g, v, nullptr, rec, n, img, st);
 }
 
 int launch_sens(const GeomDev &g, float *img, hipStream_t st) {

@@ -1,5 +1,5 @@
 // Grouping of a long list by bucket key (the transaxial line of an event)
-// for the projector pair by line.  A counting sort with one global atomic
+// for the forward projection by line.  A counting sort with one global atomic
 // per element (its rank in its bucket) runs at the rate the memory side
 // executes returning atomics, ~1e10/s: 46 ms for 5e8 events.  Here the key
 // is split into two 9-bit digits and each digit is counted per workgroup in
@@ -28,9 +28,8 @@ inline unsigned blocks_of(long long n) { return (unsigned)((n + kChunk - 1) / kC
 
 // hi_tot[h] += the elements of the workgroup's chunk with high digit h.
 __global__ __launch_bounds__(kThreads) void k_hi_count(const unsigned *__restrict__ key, long long n, unsigned nb,
-                                                       const int *flag, unsigned *hi_tot) {
+                                                       unsigned *hi_tot) {
   __shared__ unsigned h[kRadix];
-  if (flag && !*flag) return;
   for (unsigned i = threadIdx.x; i < kRadix; i += kThreads) h[i] = 0u;
   __syncthreads();
   const long long e0 = (long long)blockIdx.x * kChunk + threadIdx.x;
@@ -49,9 +48,8 @@ __global__ __launch_bounds__(kThreads) void k_hi_count(const unsigned *__restric
 
 // Exclusive prefix sum of cnt[0 .. m) into off[0 .. m] (one workgroup of
 // 1024 threads, each summing a contiguous segment).
-__global__ __launch_bounds__(1024) void k_prefix(const unsigned *cnt, long long m, const int *flag, unsigned *off) {
+__global__ __launch_bounds__(1024) void k_prefix(const unsigned *cnt, long long m, unsigned *off) {
   __shared__ unsigned part[1024];
-  if (flag && !*flag) return;
   const int t = threadIdx.x;
   const long long seg = (m + 1023) / 1024;
   const long long a = std::min(m, t * seg), b = std::min(m, a + seg);
@@ -75,13 +73,11 @@ __global__ __launch_bounds__(1024) void k_prefix(const unsigned *cnt, long long 
 
 // Pass 1: the chunk's elements go to their high-digit range hi_off[h] ..,
 // at a position reserved for the workgroup (hi_fill) plus their LDS rank.
-template <class P>
-__global__ __launch_bounds__(kThreads) void k_hi_place(const unsigned *__restrict__ key, const P *__restrict__ payload,
-                                                       long long n, unsigned nb, const int *flag,
+__global__ __launch_bounds__(kThreads) void k_hi_place(const unsigned *__restrict__ key,
+                                                       long long n, unsigned nb,
                                                        const unsigned *hi_off, unsigned *hi_fill,
-                                                       unsigned *__restrict__ tkey, P *__restrict__ tpay) {
+                                                       unsigned *__restrict__ tkey, unsigned *__restrict__ tidx) {
   __shared__ unsigned h[kRadix], base[kRadix];
-  if (flag && !*flag) return;
   for (unsigned i = threadIdx.x; i < kRadix; i += kThreads) h[i] = 0u;
   __syncthreads();
   const long long e0 = (long long)blockIdx.x * kChunk + threadIdx.x;
@@ -102,17 +98,15 @@ __global__ __launch_bounds__(kThreads) void k_hi_place(const unsigned *__restric
     const long long e = e0 + (long long)j * kThreads;
     const unsigned pos = base[kk[j] >> kDigit] + rk[j];
     tkey[pos] = kk[j];
-    tpay[pos] = payload ? payload[e] : (P)e;
+    tidx[pos] = (unsigned)e;
   }
 }
 
 // Pass 2 chunks: high-digit range h is cut into chunks of kChunk elements;
 // chunk_off[h] = the first chunk of range h (exclusive prefix of the chunk
 // counts, nhi + 1 entries; one workgroup).
-__global__ __launch_bounds__(1024) void k_chunks(const unsigned *hi_off, unsigned nhi, const int *flag,
-                                                 unsigned *chunk_off) {
+__global__ __launch_bounds__(1024) void k_chunks(const unsigned *hi_off, unsigned nhi, unsigned *chunk_off) {
   __shared__ unsigned c[kRadix + 1];
-  if (flag && !*flag) return;
   for (unsigned i = threadIdx.x; i < nhi; i += blockDim.x)
     c[i] = (hi_off[i + 1] - hi_off[i] + kChunk - 1) / kChunk;
   __syncthreads();
@@ -145,10 +139,8 @@ __device__ __forceinline__ bool chunk_range(unsigned blk, const unsigned *hi_off
 
 // Pass 2 counts: bucket totals tot[key] from the chunks' LDS counts.
 __global__ __launch_bounds__(kThreads) void k_lo_count(const unsigned *__restrict__ tkey, const unsigned *hi_off,
-                                                       const unsigned *chunk_off, unsigned nhi, const int *flag,
-                                                       unsigned *tot) {
+                                                       const unsigned *chunk_off, unsigned nhi, unsigned *tot) {
   __shared__ unsigned h[kRadix];
-  if (flag && !*flag) return;
   unsigned hi, a, b;
   if (!chunk_range(blockIdx.x, hi_off, chunk_off, nhi, hi, a, b)) return;
   for (unsigned i = threadIdx.x; i < kRadix; i += kThreads) h[i] = 0u;
@@ -163,14 +155,13 @@ __global__ __launch_bounds__(kThreads) void k_lo_count(const unsigned *__restric
     if (h[i]) atomicAdd(tot + ((hi << kDigit) | i), h[i]);
 }
 
-// Pass 2 placement: out[off[key] + reserved + LDS rank] = payload.
-template <class P>
-__global__ __launch_bounds__(kThreads) void k_lo_place(const unsigned *__restrict__ tkey, const P *__restrict__ tpay,
+// Pass 2 placement: out[off[key] + reserved + LDS rank] = the element's index.
+__global__ __launch_bounds__(kThreads) void k_lo_place(const unsigned *__restrict__ tkey,
+                                                       const unsigned *__restrict__ tidx,
                                                        const unsigned *hi_off, const unsigned *chunk_off,
-                                                       unsigned nhi, const int *flag, const unsigned *off,
-                                                       unsigned *fill, P *__restrict__ out) {
+                                                       unsigned nhi, const unsigned *off,
+                                                       unsigned *fill, unsigned *__restrict__ out) {
   __shared__ unsigned h[kRadix], base[kRadix];
-  if (flag && !*flag) return;
   unsigned hi, a, b;
   if (!chunk_range(blockIdx.x, hi_off, chunk_off, nhi, hi, a, b)) return;
   for (unsigned i = threadIdx.x; i < kRadix; i += kThreads) h[i] = 0u;
@@ -192,23 +183,25 @@ __global__ __launch_bounds__(kThreads) void k_lo_place(const unsigned *__restric
   for (int j = 0; j < kPer; ++j) {
     if (lo[j] >= kRadix) continue;
     const unsigned p = a + threadIdx.x + (unsigned)j * kThreads;
-    out[base[lo[j]] + rk[j]] = tpay[p];
+    out[base[lo[j]] + rk[j]] = tidx[p];
   }
 }
 
-template <class P>
-int group_impl(const unsigned *key, const P *payload, long long n, unsigned nb, const int *flag, P *out,
-               unsigned *off, hipStream_t st) {
+}  // namespace
+
+namespace lmk {
+
+int group_by_key(const unsigned *key, long long n, unsigned nb, unsigned *out, unsigned *off, hipStream_t st) {
   LM_REQUIRE(n >= 0 && n < (1LL << 31) && nb >= 1 && nb <= lmk::kGroupMaxBuckets, LM_EINVAL,
              "grouping: %lld elements, %u buckets", n, nb);
   const unsigned nhi = (nb + kRadix - 1) >> kDigit;
   const unsigned nbk = nhi << kDigit;  // bucket counters, whole digits
   unsigned *hi_tot = nullptr, *hi_off = nullptr, *hi_fill = nullptr, *chunk_off = nullptr, *tot = nullptr,
            *fill = nullptr, *tkey = nullptr;
-  P *tpay = nullptr;
+  unsigned *tidx = nullptr;
   auto release = [&]() {  // release errors are not reported
     for (void *q : {(void *)hi_tot, (void *)hi_off, (void *)hi_fill, (void *)chunk_off, (void *)tot, (void *)fill,
-                    (void *)tkey, (void *)tpay})
+                    (void *)tkey, (void *)tidx})
       if (q) (void)hipFreeAsync(q, st);
   };
   const size_t nn = (size_t)std::max<long long>(n, 1);
@@ -219,7 +212,7 @@ int group_impl(const unsigned *key, const P *payload, long long n, unsigned nb, 
   if (e == hipSuccess) e = hipMallocAsync((void **)&tot, nbk * sizeof(unsigned), st);
   if (e == hipSuccess) e = hipMallocAsync((void **)&fill, nbk * sizeof(unsigned), st);
   if (e == hipSuccess) e = hipMallocAsync((void **)&tkey, nn * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&tpay, nn * sizeof(P), st);
+  if (e == hipSuccess) e = hipMallocAsync((void **)&tidx, nn * sizeof(unsigned), st);
   if (e != hipSuccess) {
     release();
     (void)hipGetLastError();
@@ -235,16 +228,16 @@ int group_impl(const unsigned *key, const P *payload, long long n, unsigned nb, 
   // pass-2 chunks: at most one partial chunk per high-digit range beyond n / kChunk
   const unsigned nchunk_max = nblk + nhi;
   if (e == hipSuccess && n > 0) {
-    hipLaunchKernelGGL(k_hi_count, dim3(nblk), dim3(kThreads), 0, st, key, n, nb, flag, hi_tot);
-    hipLaunchKernelGGL(k_prefix, dim3(1), dim3(1024), 0, st, hi_tot, (long long)nhi, flag, hi_off);
-    hipLaunchKernelGGL((k_hi_place<P>), dim3(nblk), dim3(kThreads), 0, st, key, payload, n, nb, flag, hi_off,
-                       hi_fill, tkey, tpay);
-    hipLaunchKernelGGL(k_chunks, dim3(1), dim3(1024), 0, st, hi_off, nhi, flag, chunk_off);
-    hipLaunchKernelGGL(k_lo_count, dim3(nchunk_max), dim3(kThreads), 0, st, tkey, hi_off, chunk_off, nhi, flag,
+    hipLaunchKernelGGL(k_hi_count, dim3(nblk), dim3(kThreads), 0, st, key, n, nb, hi_tot);
+    hipLaunchKernelGGL(k_prefix, dim3(1), dim3(1024), 0, st, hi_tot, (long long)nhi, hi_off);
+    hipLaunchKernelGGL(k_hi_place, dim3(nblk), dim3(kThreads), 0, st, key, n, nb, hi_off,
+                       hi_fill, tkey, tidx);
+    hipLaunchKernelGGL(k_chunks, dim3(1), dim3(1024), 0, st, hi_off, nhi, chunk_off);
+    hipLaunchKernelGGL(k_lo_count, dim3(nchunk_max), dim3(kThreads), 0, st, tkey, hi_off, chunk_off, nhi,
                        tot);
-    hipLaunchKernelGGL(k_prefix, dim3(1), dim3(1024), 0, st, tot, (long long)nb, flag, off);
-    hipLaunchKernelGGL((k_lo_place<P>), dim3(nchunk_max), dim3(kThreads), 0, st, tkey, tpay, hi_off, chunk_off,
-                       nhi, flag, off, fill, out);
+    hipLaunchKernelGGL(k_prefix, dim3(1), dim3(1024), 0, st, tot, (long long)nb, off);
+    hipLaunchKernelGGL(k_lo_place, dim3(nchunk_max), dim3(kThreads), 0, st, tkey, tidx, hi_off, chunk_off,
+                       nhi, off, fill, out);
     e = hipGetLastError();
   } else if (e == hipSuccess) {
     e = hipMemsetAsync(off, 0, ((size_t)nb + 1) * sizeof(unsigned), st);
@@ -255,26 +248,6 @@ int group_impl(const unsigned *key, const P *payload, long long n, unsigned nb, 
     return LM_EHIP;
   }
   return LM_OK;
-}
-
-}  // namespace
-
-namespace lmk {
-
-size_t group_temp_bytes(long long n, unsigned nb, size_t payload_bytes) {
-  const size_t nbk = (size_t)((nb + kRadix - 1) >> kDigit) << kDigit;
-  return (size_t)std::max<long long>(n, 1) * (sizeof(unsigned) + payload_bytes) + 2 * nbk * sizeof(unsigned) +
-         4 * (kRadix + 1) * sizeof(unsigned);
-}
-
-int group_by_key(const unsigned *key, const unsigned *payload, long long n, unsigned nb, const int *flag,
-                 unsigned *out, unsigned *off, hipStream_t st) {
-  return group_impl(key, payload, n, nb, flag, out, off, st);
-}
-
-int group_by_key(const unsigned *key, const unsigned long long *payload, long long n, unsigned nb, const int *flag,
-                 unsigned long long *out, unsigned *off, hipStream_t st) {
-  return group_impl(key, payload, n, nb, flag, out, off, st);
 }
 
 }  // namespace lmk

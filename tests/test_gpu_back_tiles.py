@@ -1,5 +1,5 @@
 """GPU parity of the back projection by image tile (lists of at least 32768
-events, below the lists that go by transaxial line) against the FP64 oracle:
+events) against the FP64 oracle:
 images around the 16-voxel tile edge, odd and single-slice grids, unequal
 voxel sides, with and without TOF, and values that are not finite.
 Tolerance as for every back projection: ||gpu - orc||_inf <= 1e-4
@@ -26,8 +26,7 @@ def P():
 
 
 def _geometry(P, n, h, tof, n_cry=96, n_ring=12, fwhm=30.0):
-    """A cylinder of many lines (no list here has 64 events per line) around
-    a box of n voxels of h mm."""
+    """A cylinder around a box of n voxels of h mm."""
     half = 0.5 * np.asarray(n) * np.asarray(h)
     radius = 1.3 * float(np.hypot(half[0], half[1]))
     n_ring = 1 if n[2] == 1 else n_ring
