@@ -7,10 +7,10 @@
 //
 // The EM step reuses the projector pair (bricked image, the events of the
 // subset stored contiguously).  The denoising works on row-major images:
-// each of its iterations is one pass for the dual step (forward
-// differences of ubar, projection onto the unit balls) and one for the
-// primal step (adjoint stencil, weighted prox, extrapolation); both stream
-// whole images and are bound by HBM bandwidth.  The step sizes of all
+// each of its iterations is one pass marching along z (the dual step: forward
+// differences of ubar, projection onto the unit balls; and the primal step:
+// adjoint stencil, weighted prox, extrapolation), bound by the bandwidth of
+// HBM and of the memory-side cache.  The step sizes of all
 // iterations are computed on the device from the smallest finite weight,
 // so a call never waits for the device.
 #include <hip/hip_runtime.h>
@@ -66,33 +66,33 @@ __global__ void k_fill_u32(unsigned *__restrict__ p, long long n, unsigned v) {
     p[i] = v;
 }
 
-// EM image z = x n bp / g (0 where g = 0).  With beta > 0 also the weights
-// w = g / (beta x) (inf where x = 0), the start of the denoising (u = ubar
-// = z, q = 0) and the smallest weight of each block in part[blockIdx.x]
-// (as float bits: non-negative floats order like their bits).  With
-// beta = 0, x <- z.
+// The dual variable of the denoising, one image per component.
+struct Dual {
+  float *q[3];
+};
+
+// EM image z = x n bp / g (0 where g = 0), x <- z.  With beta > 0 also the
+// weights w = g / (beta x) (inf where x = 0), the start of the denoising (u =
+// ubar = z, with u in x; q = 0) and the smallest weight of each block in
+// part[blockIdx.x] (as float bits: non-negative floats order like their
+// bits).
 __global__ __launch_bounds__(kBlock) void k_em_image(float *__restrict__ x, const float *__restrict__ bp,
                                                      const float *__restrict__ g, long long nv, float nsub,
                                                      float beta, float *__restrict__ z, float *__restrict__ w,
-                                                     float *__restrict__ u, float *__restrict__ ubar,
-                                                     float *__restrict__ q, unsigned *__restrict__ part) {
+                                                     float *__restrict__ ubar, Dual q, unsigned *__restrict__ part) {
   __shared__ unsigned red[kBlock / 64];
   unsigned lo = kInfBits;
   for (long long j = (long long)blockIdx.x * kBlock + threadIdx.x; j < nv; j += (long long)gridDim.x * kBlock) {
     const float xj = x[j], gj = g[j];
     const float zj = gj > 0.0f ? xj * nsub * bp[j] / gj : 0.0f;
+    x[j] = zj;
     if (beta > 0.0f) {
       const float wj = xj > 0.0f ? gj / (beta * xj) : INFINITY;
       z[j] = zj;
       w[j] = wj;
-      u[j] = zj;
       ubar[j] = zj;
-      q[j] = 0.0f;
-      q[nv + j] = 0.0f;
-      q[2 * nv + j] = 0.0f;
+      for (int c = 0; c < 3; ++c) q.q[c][j] = 0.0f;
       lo = min(lo, __float_as_uint(wj));
-    } else {
-      x[j] = zj;
     }
   }
   if (beta <= 0.0f) return;
@@ -130,64 +130,207 @@ __global__ __launch_bounds__(kBlock) void k_pd_schedule(const unsigned *__restri
   }
 }
 
-// Dual step: q <- projection of q + sigma_k K ubar onto the unit ball of
-// each voxel (K = forward differences, zero in the last layer).
-__global__ __launch_bounds__(kBlock) void k_pd_dual(const float *__restrict__ ubar, float *__restrict__ q, int nx,
-                                                    int ny, int nz, const float4 *__restrict__ sched, int k) {
-  // images have at most 512^3 voxels: 32-bit indices, also for the three
-  // components of q
-  const unsigned nxy = (unsigned)nx * ny, nv = nxy * nz;
-  const float sigma = sched[k].y;
-  for (unsigned j = blockIdx.x * kBlock + threadIdx.x; j < nv; j += gridDim.x * kBlock) {
-    const unsigned row = j / nx;
-    const int ix = (int)(j - row * nx), iy = (int)(row % ny), iz = (int)(row / ny);
-    const float c = ubar[j];
-    const float gx = ix + 1 < nx ? ubar[j + 1] - c : 0.0f;
-    const float gy = iy + 1 < ny ? ubar[j + nx] - c : 0.0f;
-    const float gz = iz + 1 < nz ? ubar[j + nxy] - c : 0.0f;
-    const float a = fmaf(sigma, gx, q[j]), b = fmaf(sigma, gy, q[nv + j]), d = fmaf(sigma, gz, q[2 * nv + j]);
-    const float r = 1.0f / fmaxf(1.0f, sqrtf(a * a + b * b + d * d));
-    q[j] = a * r;
-    q[nv + j] = b * r;
-    q[2 * nv + j] = d * r;
+// One iteration of the denoising, marching along z:
+//   q+ = projection of q + sigma_k K ubar onto the unit ball of each voxel
+//        (K = forward differences, zero in the last layer),
+//   v = u - tau_k K^T q+,  u+ = max(0, (v + tau_k w z) / (1 + tau_k w)) (z
+//        where w = inf),  ubar+ = u+ + theta_k (u+ - u).
+// A block owns a column of 64 x 4 voxels (rows of 256 bytes) and a run of CZ
+// planes.  K^T q+ needs q+ at the three lower neighbours: the thread's own
+// value of the plane below (z), LDS (x, y), or the dual step of the column's
+// left and front faces, which threads 0 .. 67 repeat; the plane below the
+// run is computed first.  Planes k and k + 1 of ubar with a one-voxel ring
+// are in LDS, plane k + 2 in registers; q, u, z and w of the next plane are
+// loaded a step ahead.  ubar and q are read from one set of images and written to
+// another (neighbouring blocks read them); u is the thread's own.
+//
+// 48 bytes per voxel, where a dual and a primal pass took 60 (q went to
+// memory and back between them): 200x200x96, 48.8 -> 34.8 us, 5.3 TB/s, which is
+// what a copy of this size reaches.  Columns are dealt so that each XCD works
+// on a contiguous run: the lines of the ring and the faces, as many as the
+// column's own, are then in its L2 (in the launch order of the blocks 54.6 us).
+constexpr int kPX = 64, kPY = 4;  // the column
+
+template <int CZ>
+__global__ __launch_bounds__(kBlock) void k_pd_march(const float *__restrict__ ubar, Dual q, Dual qo, float *u,
+                                                     const float *__restrict__ z, const float *__restrict__ w,
+                                                     float *__restrict__ ubar_out, int nx, int ny, int nz,
+                                                     const float4 *__restrict__ sched, int it) {
+  static_assert(kPX * kPY == kBlock, "one thread per voxel of a plane");
+  constexpr int RX = kPX + 2, RY = kPY + 2;        // box of ubar with its ring
+  constexpr int kRing = RX * RY - kBlock, kFace = kPX + kPY;
+  __shared__ float ub[2][RX * RY];
+  __shared__ float s0[kPY][kPX + 1], s1[kPY + 1][kPX];
+  const int t = threadIdx.x, ti = t % kPX, tj = t / kPX;
+  const int ntx = (nx + kPX - 1) / kPX, nty = (ny + kPY - 1) / kPY;
+  int blk = blockIdx.x;
+  const int full = (int)gridDim.x & ~7;
+  if (blk < full) blk = (blk & 7) * (full >> 3) + (blk >> 3);
+  const int x0 = blk % ntx * kPX, y0 = blk / ntx % nty * kPY;
+  const int kz0 = blk / (ntx * nty) * CZ, kz1 = min(nz, kz0 + CZ);
+  const int i = x0 + ti, j = y0 + tj;
+  const bool own = i < nx && j < ny;
+  // images have at most 512^3 voxels: 32-bit indices
+  const unsigned nxy = (unsigned)nx * ny;
+  const unsigned at = own ? (unsigned)j * nx + i : 0u;
+  const int ob = (ti + 1) + RX * (tj + 1);
+  // ring cell of thread t < kRing: front row, back row, left and right columns
+  int rb = 0;
+  unsigned r_at = 0;
+  bool r_ok = false;
+  if (t < kRing) {
+    int bx, by;
+    if (t < RX) { bx = t; by = 0; }
+    else if (t < 2 * RX) { bx = t - RX; by = RY - 1; }
+    else { bx = (t - 2 * RX) & 1 ? RX - 1 : 0; by = 1 + (t - 2 * RX) / 2; }
+    rb = bx + RX * by;
+    const int gi = x0 - 1 + bx, gj = y0 - 1 + by;
+    r_ok = gi >= 0 && gi < nx && gj >= 0 && gj < ny;
+    r_at = r_ok ? (unsigned)gj * nx + gi : 0u;
+  }
+  // face voxel of thread t < kFace: left column (component 0), front row (1)
+  int fb = 0, fi = 0, fj = 0;
+  unsigned f_at = 0;
+  bool f_ok = false;
+  if (t < kFace) {
+    const int bx = t < kPY ? 0 : t - kPY + 1, by = t < kPY ? t + 1 : 0;
+    fb = bx + RX * by;
+    fi = x0 - 1 + bx;
+    fj = y0 - 1 + by;
+    f_ok = fi >= 0 && fi < nx && fj >= 0 && fj < ny;
+    f_at = f_ok ? (unsigned)fj * nx + fi : 0u;
+  }
+  const float4 st = sched[it];
+  const float tau = st.x, sigma = st.y, theta = st.z;
+  auto own_at = [&](int k) { return own && k < nz ? ubar[at + (unsigned)k * nxy] : 0.0f; };
+  auto ring_at = [&](int k) { return r_ok && k < nz ? ubar[r_at + (unsigned)k * nxy] : 0.0f; };
+  // the dual step at box position b of voxel (vi, vj, k): planes k and k + 1 of ubar in lo and up
+  auto dual = [&](const float *lo, float upv, int b, int vi, int vj, int k, const float (&qv)[3], float (&qn)[3]) {
+    const float c = lo[b];
+    const float gx = vi + 1 < nx ? lo[b + 1] - c : 0.0f;
+    const float gy = vj + 1 < ny ? lo[b + RX] - c : 0.0f;
+    const float gz = k + 1 < nz ? upv - c : 0.0f;
+    const float a0 = fmaf(sigma, gx, qv[0]), a1 = fmaf(sigma, gy, qv[1]), a2 = fmaf(sigma, gz, qv[2]);
+    const float r = 1.0f / fmaxf(1.0f, sqrtf(a0 * a0 + a1 * a1 + a2 * a2));
+    qn[0] = a0 * r;
+    qn[1] = a1 * r;
+    qn[2] = a2 * r;
+  };
+  auto load_q = [&](bool ok, unsigned p, float (&v)[3]) {
+    for (int c = 0; c < 3; ++c) v[c] = ok ? q.q[c][p] : 0.0f;
+  };
+  float below = 0.0f;  // q+ along z of the plane below
+  if (kz0 > 0) {
+    const int k = kz0 - 1;
+    ub[0][ob] = own_at(k);
+    if (t < kRing) ub[0][rb] = ring_at(k);
+    const float up = own_at(kz0);
+    float qv[3], qn[3];
+    load_q(own, at + (unsigned)k * nxy, qv);
+    __syncthreads();
+    dual(ub[0], up, ob, i, j, k, qv, qn);
+    below = qn[2];
+    __syncthreads();
+  }
+  ub[0][ob] = own_at(kz0);
+  ub[1][ob] = own_at(kz0 + 1);
+  if (t < kRing) {
+    ub[0][rb] = ring_at(kz0);
+    ub[1][rb] = ring_at(kz0 + 1);
+  }
+  float po = own_at(kz0 + 2), pr = ring_at(kz0 + 2);
+  float qv[3], fq[3], uv = 0.0f, zv = 0.0f, wv = 0.0f;
+  {
+    const unsigned p = at + (unsigned)kz0 * nxy;
+    load_q(own, p, qv);
+    load_q(f_ok, f_at + (unsigned)kz0 * nxy, fq);
+    if (own) {
+      uv = u[p];
+      zv = z[p];
+      wv = w[p];
+    }
+  }
+  __syncthreads();
+  int lo = 0;  // LDS buffer of plane k
+  for (int k = kz0; k < kz1; ++k, lo ^= 1) {
+    // loads of the next step
+    const float no = own_at(k + 3), nr = ring_at(k + 3);
+    const bool more = k + 1 < kz1;
+    const unsigned pn = at + (unsigned)(k + 1) * nxy;
+    float nq[3], nfq[3], nu = 0.0f, nzv = 0.0f, nw = 0.0f;
+    load_q(own && more, pn, nq);
+    load_q(f_ok && more, f_at + (unsigned)(k + 1) * nxy, nfq);
+    if (own && more) {
+      nu = u[pn];
+      nzv = z[pn];
+      nw = w[pn];
+    }
+    const float *pl = ub[lo], *pu = ub[lo ^ 1];
+    const unsigned p = at + (unsigned)k * nxy;
+    float qn[3];
+    dual(pl, pu[ob], ob, i, j, k, qv, qn);
+    s0[tj][ti + 1] = qn[0];
+    s1[tj + 1][ti] = qn[1];
+    if (own)
+      for (int c = 0; c < 3; ++c) qo.q[c][p] = qn[c];
+    if (t < kFace) {
+      float fn[3] = {0.0f, 0.0f, 0.0f};
+      if (f_ok) dual(pl, pu[fb], fb, fi, fj, k, fq, fn);
+      if (t < kPY) s0[t][0] = fn[0];
+      else s1[0][t - kPY] = fn[1];
+    }
+    __syncthreads();
+    // plane k + 2 takes the buffer of plane k
+    ub[lo][ob] = po;
+    if (t < kRing) ub[lo][rb] = pr;
+    po = no;
+    pr = nr;
+    if (own) {
+      float kt = 0.0f;
+      if (i > 0) kt += s0[tj][ti];
+      if (i + 1 < nx) kt -= qn[0];
+      if (j > 0) kt += s1[tj][ti];
+      if (j + 1 < ny) kt -= qn[1];
+      if (k > 0) kt += below;
+      if (k + 1 < nz) kt -= qn[2];
+      float un;
+      if (isinf(wv)) {
+        un = zv;
+      } else {
+        const float v = fmaf(-tau, kt, uv);
+        const float tw = tau * wv;
+        un = fmaxf(0.0f, fmaf(tw, zv, v) / (1.0f + tw));
+      }
+      u[p] = un;
+      ubar_out[p] = fmaf(theta, un - uv, un);
+    }
+    below = qn[2];
+    for (int c = 0; c < 3; ++c) {
+      qv[c] = nq[c];
+      fq[c] = nfq[c];
+    }
+    uv = nu;
+    zv = nzv;
+    wv = nw;
+    __syncthreads();
   }
 }
 
-// Primal step and extrapolation: v = u - tau_k K^T q,
-// u+ = max(0, (v + tau_k w z) / (1 + tau_k w)) (u+ = z where w = inf),
-// ubar = u+ + theta_k (u+ - u).  u is read and written at the thread's own
-// voxel only; u_out may be u (or, in the last iteration, the caller's x).
-__global__ __launch_bounds__(kBlock) void k_pd_primal(const float *u, const float *__restrict__ q,
-                                                      const float *__restrict__ z, const float *__restrict__ w,
-                                                      float *u_out, float *__restrict__ ubar, int nx, int ny, int nz,
-                                                      const float4 *__restrict__ sched, int k) {
-  const unsigned nxy = (unsigned)nx * ny, nv = nxy * nz;
-  const float4 st = sched[k];
-  const float tau = st.x, theta = st.z;
-  for (unsigned j = blockIdx.x * kBlock + threadIdx.x; j < nv; j += gridDim.x * kBlock) {
-    const unsigned row = j / nx;
-    const int ix = (int)(j - row * nx), iy = (int)(row % ny), iz = (int)(row / ny);
-    // (K^T q)_j = sum over axes of q_a[j - e_a] (if j has a lower neighbour)
-    // minus q_a[j] (unless j is in the last layer)
-    float kt = 0.0f;
-    if (ix > 0) kt += q[j - 1];
-    if (ix + 1 < nx) kt -= q[j];
-    if (iy > 0) kt += q[nv + j - nx];
-    if (iy + 1 < ny) kt -= q[nv + j];
-    if (iz > 0) kt += q[2 * nv + j - nxy];
-    if (iz + 1 < nz) kt -= q[2 * nv + j];
-    const float uj = u[j], zj = z[j], wj = w[j];
-    float up;
-    if (isinf(wj)) {
-      up = zj;
-    } else {
-      const float v = fmaf(-tau, kt, uj);
-      const float tw = tau * wj;
-      up = fmaxf(0.0f, fmaf(tw, zj, v) / (1.0f + tw));
-    }
-    u_out[j] = up;
-    ubar[j] = fmaf(theta, up - uj, up);
-  }
+// An iteration's launch: runs of 16 planes where that leaves three blocks per
+// CU and more (200x200x96: 34.8 us, runs of 8 35.9, of 32 45.9), of 4 on
+// smaller images (each run repeats the dual step of the plane below it).
+int launch_pd(const float *ubar, const Dual &q, const Dual &qo, float *u, const float *z, const float *w,
+              float *ubar_out, const int n[3], const float4 *sched, int it, hipStream_t st) {
+  const long long cols = (long long)((n[0] + kPX - 1) / kPX) * ((n[1] + kPY - 1) / kPY);
+  auto runs = [&](int cz) { return cols * ((n[2] + cz - 1) / cz); };
+  if (runs(16) >= 768)
+    hipLaunchKernelGGL((k_pd_march<16>), dim3((unsigned)runs(16)), dim3(kBlock), 0, st, ubar, q, qo, u, z, w,
+                       ubar_out, n[0], n[1], n[2], sched, it);
+  else
+    hipLaunchKernelGGL((k_pd_march<4>), dim3((unsigned)runs(4)), dim3(kBlock), 0, st, ubar, q, qo, u, z, w, ubar_out,
+                       n[0], n[1], n[2], sched, it);
+  LM_TRY_HIP(hipGetLastError());
+  return LM_OK;
 }
 
 // Stream-ordered device temporaries of one call, freed (stream-ordered)
@@ -258,6 +401,7 @@ int lm_emtv(const lm_geom *G, const int16_t *ev, const float *s, int64_t n, int3
   float *z = nullptr, *w = nullptr, *u = nullptr, *ubar = nullptr, *q3 = nullptr;
   float4 *sched = nullptr;
   unsigned *part = nullptr;
+  Dual qa{}, qb{};
   const unsigned img_grid = grid_for(nv);
   if (int rc = t.get(&evs, 5 * n)) return rc;
   if (int rc = t.get(&ss, n)) return rc;
@@ -271,6 +415,10 @@ int lm_emtv(const lm_geom *G, const int16_t *ev, const float *s, int64_t n, int3
     if (int rc = t.get(&u, nv)) return rc;
     if (int rc = t.get(&ubar, nv)) return rc;
     if (int rc = t.get(&q3, 3 * nv)) return rc;
+    // the second set of ubar and q: images that are free while the denoising
+    // runs (its u lives in x)
+    qa = Dual{{q3, q3 + nv, q3 + 2 * nv}};
+    qb = Dual{{xb, bpb, u}};
     if (int rc = t.get(&part, img_grid)) return rc;
     if (int rc = t.get(&sched, std::max(iters, 1))) return rc;
   }
@@ -296,23 +444,15 @@ int lm_emtv(const lm_geom *G, const int16_t *ev, const float *s, int64_t n, int3
       }
       if (int rc = lmk::launch_from_layout(gd.n, gb.lay, 1, bpb, bp, st)) return rc;
       hipLaunchKernelGGL(k_em_image, dim3(img_grid), dim3(kBlock), 0, st, x, bp, g, nv, (float)n_subsets, beta, z,
-                         w, u, ubar, q3, part);
+                         w, ubar, qa, part);
       LM_TRY_HIP(hipGetLastError());
-      if (!denoise) continue;
-      if (iters == 0) {
-        LM_TRY_HIP(hipMemcpyAsync(x, z, (size_t)nv * sizeof(float), hipMemcpyDeviceToDevice, st));
-        continue;
-      }
+      if (iters == 0) continue;
       hipLaunchKernelGGL(k_pd_schedule, dim3(1), dim3(kBlock), 0, st, part, (int)img_grid, tau0, iters, sched);
       LM_TRY_HIP(hipGetLastError());
+      float *ua = ubar, *ub = bp;
       for (int k = 0; k < iters; ++k) {
-        hipLaunchKernelGGL(k_pd_dual, dim3(grid_for(nv)), dim3(kBlock), 0, st, ubar, q3, gd.n[0], gd.n[1], gd.n[2],
-                           sched, k);
-        LM_TRY_HIP(hipGetLastError());
-        float *dst = k + 1 == iters ? x : u;
-        hipLaunchKernelGGL(k_pd_primal, dim3(grid_for(nv)), dim3(kBlock), 0, st, u, q3, z, w, dst, ubar, gd.n[0],
-                           gd.n[1], gd.n[2], sched, k);
-        LM_TRY_HIP(hipGetLastError());
+        if (int rc = launch_pd(ua, k % 2 ? qb : qa, k % 2 ? qa : qb, x, z, w, ub, gd.n, sched, k, st)) return rc;
+        std::swap(ua, ub);
       }
     }
   }
