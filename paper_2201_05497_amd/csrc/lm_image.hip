@@ -563,14 +563,19 @@ int launch_tv_fused(const int n[3], const Layout &L, int ncomp, const float *x, 
                     float inv_p, bool fuse, hipStream_t st) {
   const long long ne = layout_size(L);
   if (prior_march_ok(L, ncomp)) {
-    constexpr int CZ = 16;
-    const int nblocks = ((n[0] + 15) / 16) * ((n[1] + 15) / 16) * ((n[2] + CZ - 1) / CZ);
-    if (xi)
-      hipLaunchKernelGGL((k_tv_march<CZ, true>), dim3(nblocks), dim3(kBlock), 0, st, x, w, xi, w_out, z, x_out, T,
-                         zbar, L.nbx, L.nby, n[0], n[1], n[2], ne, Sp, beta, inv_p, fuse ? 1 : 0, nblocks);
-    else
-      hipLaunchKernelGGL((k_tv_march<CZ, false>), dim3(nblocks), dim3(kBlock), 0, st, x, w, xi, w_out, z, x_out, T,
-                         zbar, L.nbx, L.nby, n[0], n[1], n[2], ne, Sp, beta, inv_p, fuse ? 1 : 0, nblocks);
+    const int cols = ((n[0] + 15) / 16) * ((n[1] + 15) / 16);
+    auto march = [&](auto kernel, int cz) {
+      const int nblocks = cols * ((n[2] + cz - 1) / cz);
+      hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kBlock), 0, st, x, w, xi, w_out, z, x_out, T, zbar, L.nbx, L.nby,
+                         n[0], n[1], n[2], ne, Sp, beta, inv_p, fuse ? 1 : 0, nblocks);
+    };
+    // runs of 16 planes where that leaves three blocks per CU and more
+    // (200x200x96: 31.7 us, runs of 2 34.1), of 2 on smaller images, which
+    // repeat the dual step of every other plane but fill the chip (128x128x48:
+    // 10.7 us, runs of 16 21.2; 160x160x96: 23.5 against 26.3)
+    const bool long_runs = cols * ((n[2] + 15) / 16) >= 768;
+    if (xi) long_runs ? march(k_tv_march<16, true>, 16) : march(k_tv_march<2, true>, 2);
+    else long_runs ? march(k_tv_march<16, false>, 16) : march(k_tv_march<2, false>, 2);
   } else if (xi) {
     lmh::set_error("prior update by column march: the image layout must be 4x4x4 bricks with 3 components");
     return LM_EINVAL;
