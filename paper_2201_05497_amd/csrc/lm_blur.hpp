@@ -31,10 +31,11 @@ int launch_blur(const int n[3], const Layout &L, long long ne, const Blur &b, co
 
 // The z step of Algorithm 2 after a data update under the resolution
 // model: dzb = B dz, z += dzb, zbar = z + dzb inv_p, fuse ? x = max(0, x -
-// T zbar) (in place) : store zbar, and dz = 0.  The last blur pass carries
-// the z step; t1, t2 are temporaries of ne elements.
+// T zbar) (in place) : store zbar.  With clear, dz = 0 for the next
+// update's atomics; without, dz holds no value to rely on.  The last blur pass
+// carries the z step; t1, t2 are temporaries of ne elements.
 int launch_blur_dual_image(const int n[3], const Layout &L, long long ne, const Blur &b, float *dz, float *t1,
                            float *t2, float *z, float *x, const float *T, float *zbar, float inv_p, bool fuse,
-                           hipStream_t st);
+                           bool clear, hipStream_t st);
 
 }  // namespace lmk

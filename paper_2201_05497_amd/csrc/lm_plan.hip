@@ -644,7 +644,7 @@ int lm_spdhg_epoch(lm_plan *p, float *x, const int32_t *seq, int32_t n_updates, 
           return rc;
         if (int rc = timed(p, LM_K_DUAL_IMAGE, st, [&] {
               return lmk::launch_blur_dual_image(p->G.n, p->lay, E, p->blur, p->dz, p->bt1, p->bt2, p->z, xi, p->T,
-                                                 p->zbar, inv_p_data, fuse, st);
+                                                 p->zbar, inv_p_data, fuse, false, st);
             }))
           return rc;
       } else if (!p->blur.on) {
@@ -666,7 +666,7 @@ int lm_spdhg_epoch(lm_plan *p, float *x, const int32_t *seq, int32_t n_updates, 
           return rc;
         if (int rc = timed(p, LM_K_DUAL_IMAGE, st, [&] {
               return lmk::launch_blur_dual_image(p->G.n, p->lay, E, p->blur, p->dz, p->bt1, p->bt2, p->z, xi, p->T,
-                                                 p->zbar, inv_p_data, fuse, st);
+                                                 p->zbar, inv_p_data, fuse, true, st);
             }))
           return rc;
       }
