@@ -337,25 +337,16 @@ int launch_pd(const float *ubar, const Dual &q, const Dual &qo, float *u, const 
 // when the call returns.
 struct Temps {
   hipStream_t st;
-  void *p[16] = {};
-  int n = 0;
+  void *p = nullptr;
   explicit Temps(hipStream_t s) : st(s) {}
-  template <class T>
-  int get(T **out, long long count) {
-    *out = nullptr;
-    if (count <= 0) return LM_OK;
-    void *q = nullptr;
-    const hipError_t e = hipMallocAsync(&q, (size_t)count * sizeof(T), st);
-    if (e != hipSuccess) {
-      lmh::set_error("lm_emtv temporary of %lld bytes: %s", (long long)(count * sizeof(T)), hipGetErrorString(e));
-      return e == hipErrorOutOfMemory ? LM_ENOMEM : LM_EHIP;
-    }
-    p[n++] = q;
-    *out = static_cast<T *>(q);
-    return LM_OK;
+  int get(lmh::Slab &arrays) {
+    const hipError_t e = arrays.alloc(st, &p);
+    if (e == hipSuccess) return LM_OK;
+    lmh::set_error("lm_emtv temporaries of %zu bytes: %s", arrays.bytes(), hipGetErrorString(e));
+    return e == hipErrorOutOfMemory ? LM_ENOMEM : LM_EHIP;
   }
   ~Temps() {
-    for (int i = 0; i < n; ++i) (void)hipFreeAsync(p[i], st);  // a release error has no caller to go to
+    if (p) (void)hipFreeAsync(p, st);  // a release error has no caller to go to
   }
 };
 
@@ -403,24 +394,24 @@ int lm_emtv(const lm_geom *G, const int16_t *ev, const float *s, int64_t n, int3
   unsigned *part = nullptr;
   Dual qa{}, qb{};
   const unsigned img_grid = grid_for(nv);
-  if (int rc = t.get(&evs, 5 * n)) return rc;
-  if (int rc = t.get(&ss, n)) return rc;
-  if (int rc = t.get(&qe, m_max)) return rc;
-  if (int rc = t.get(&xb, nb)) return rc;
-  if (int rc = t.get(&bpb, nb)) return rc;
-  if (int rc = t.get(&bp, nv)) return rc;
+  lmh::Slab arrays;
+  arrays.add(&evs, 5 * n);
+  arrays.add(&ss, n);
+  arrays.add(&qe, m_max);
+  for (float **q : {&xb, &bpb}) arrays.add(q, nb);
+  arrays.add(&bp, nv);
   if (denoise) {
-    if (int rc = t.get(&z, nv)) return rc;
-    if (int rc = t.get(&w, nv)) return rc;
-    if (int rc = t.get(&u, nv)) return rc;
-    if (int rc = t.get(&ubar, nv)) return rc;
-    if (int rc = t.get(&q3, 3 * nv)) return rc;
+    for (float **q : {&z, &w, &u, &ubar}) arrays.add(q, nv);
+    arrays.add(&q3, 3 * nv);
+    arrays.add(&part, img_grid);
+    arrays.add(&sched, iters);
+  }
+  if (int rc = t.get(arrays)) return rc;
+  if (denoise) {
     // the second set of ubar and q: images that are free while the denoising
     // runs (its u lives in x)
     qa = Dual{{q3, q3 + nv, q3 + 2 * nv}};
     qb = Dual{{xb, bpb, u}};
-    if (int rc = t.get(&part, img_grid)) return rc;
-    if (int rc = t.get(&sched, std::max(iters, 1))) return rc;
   }
   if (n > 0) {
     hipLaunchKernelGGL(k_subset_order, dim3(grid_for(n)), dim3(kBlock), 0, st, ev, s, (long long)n, (int)n_subsets,

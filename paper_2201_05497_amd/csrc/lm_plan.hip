@@ -332,17 +332,15 @@ Sizes plan_sizes(long long n, int nsub, long long nvox, long long ne, int ncomp)
   return s;
 }
 
-template <class T>
-int dalloc(lm_plan *p, T **ptr, size_t count) {
+// Allocates the arrays of `s` for the life of the plan.
+int dalloc(lm_plan *p, lmh::Slab &s) {
   void *q = nullptr;
-  const size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
-  const hipError_t e = hipMallocAsync(&q, bytes, p->last);
+  const hipError_t e = s.alloc(p->last, &q);
   if (e != hipSuccess) {
-    lmh::set_error("hipMallocAsync(%zu bytes) failed: %s", bytes, hipGetErrorString(e));
+    lmh::set_error("hipMallocAsync(%zu bytes) failed: %s", s.bytes(), hipGetErrorString(e));
     return LM_ENOMEM;
   }
   p->allocs.push_back(q);
-  *ptr = static_cast<T *>(q);
   return LM_OK;
 }
 
@@ -474,32 +472,29 @@ int lm_plan_create(const lm_geom *G, const int16_t *ev, const float *s, int64_t 
     free_plan(p);
     return code;
   };
-  if ((rc = dalloc(p, &p->rec, N)) || (rc = dalloc(p, &p->S, N)) || (rc = dalloc(p, &p->mu, N)) ||
-      (rc = dalloc(p, &p->c, N)) || (rc = dalloc(p, &p->P1, N)) || (rc = dalloc(p, &p->tmp, N)) ||
-      (rc = dalloc(p, &p->perm, N)) || (rc = dalloc(p, &p->off_d, n_sub + 1)) ||
-      (rc = dalloc(p, &p->gimg, E)) || (rc = dalloc(p, &p->T, E)) || (rc = dalloc(p, &p->z, E)) ||
-      (rc = dalloc(p, &p->zbar, E)) || (rc = dalloc(p, &p->dz, E)) || (rc = dalloc(p, &p->xint, E)) ||
-      (rc = dalloc(p, &p->xalt, E)) ||
-      (rc = dalloc(p, &p->w, E * p->ncomp)) || (rc = dalloc(p, &p->wn, E * p->ncomp)))
-    return fail(rc);
+  lmh::Slab lists;
+  lists.add(&p->rec, N);
+  for (float **q : {&p->S, &p->mu, &p->c, &p->P1, &p->tmp}) lists.add(q, N);
+  lists.add(&p->perm, N);
+  lists.add(&p->off_d, n_sub + 1);
+  for (float **q : {&p->gimg, &p->T, &p->z, &p->zbar, &p->dz, &p->xint, &p->xalt}) lists.add(q, E);
+  for (float **q : {&p->w, &p->wn}) lists.add(q, E * p->ncomp);
+  if ((rc = dalloc(p, lists))) return fail(rc);
 
   // temporaries: hash table, slots, ones image (bricks)
   const unsigned long long cap = hash_capacity(N);
   unsigned long long *keys = nullptr;
   unsigned *cnt = nullptr, *slot = nullptr;
   float *ones = nullptr;
-  hipError_t e = hipMallocAsync((void **)&keys, cap * sizeof(unsigned long long), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&cnt, cap * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&slot, std::max<long long>(N, 1) * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&ones, E * sizeof(float), st);
-  auto free_tmp = [&]() {  // release errors are not reported
-    if (keys) (void)hipFreeAsync(keys, st);
-    if (cnt) (void)hipFreeAsync(cnt, st);
-    if (slot) (void)hipFreeAsync(slot, st);
-    if (ones) (void)hipFreeAsync(ones, st);
-  };
+  lmh::Slab temporaries;
+  temporaries.add(&keys, cap);
+  temporaries.add(&cnt, cap);
+  temporaries.add(&slot, N);
+  temporaries.add(&ones, E);
+  void *tmp = nullptr;
+  const hipError_t e = temporaries.alloc(st, &tmp);
+  auto free_tmp = [&]() { (void)hipFreeAsync(tmp, st); };  // release errors are not reported
   if (e != hipSuccess) {
-    free_tmp();
     lmh::set_error("temporary allocation failed: %s", hipGetErrorString(e));
     return fail(LM_ENOMEM);
   }
@@ -722,7 +717,9 @@ int lm_plan_set_event_factors(lm_plan *p, const float *m, void *stream) {
   (void)hipFreeAsync(d, st);
   LM_TRY_HIP(e);
   LM_REQUIRE(h == 0, LM_ERANGE, "%llu event factors are not positive and finite", h);
-  if (int rc = dalloc(p, &p->mfac, (size_t)N)) return rc;
+  lmh::Slab factors;
+  factors.add(&p->mfac, N);
+  if (int rc = dalloc(p, factors)) return rc;
   hipLaunchKernelGGL(k_apply_factors, dim3(grid_for(N)), dim3(kBlock), 0, st, m, p->perm, p->rec, p->mu, p->mfac, N);
   LM_TRY_HIP(hipGetLastError());
   LM_TRY_HIP(hipStreamSynchronize(st));
@@ -739,10 +736,9 @@ int lm_plan_set_resolution(lm_plan *p, const double fwhm_vox[3], void *stream) {
   p->last = st;
   const long long N = p->n, E = p->ne;
   if (b.on && !p->xb) {
-    int rc;
-    if ((rc = dalloc(p, &p->xb, (size_t)E)) || (rc = dalloc(p, &p->dzb, (size_t)E)) ||
-        (rc = dalloc(p, &p->bt1, (size_t)E)) || (rc = dalloc(p, &p->bt2, (size_t)E)))
-      return rc;
+    lmh::Slab images;
+    for (float **q : {&p->xb, &p->dzb, &p->bt1, &p->bt2}) images.add(q, E);
+    if (int rc = dalloc(p, images)) return rc;
   }
   p->blur = b;
   // P^LM 1 and S_e = gamma rho / (P^LM 1)_e of the operator G B
@@ -766,7 +762,9 @@ int lm_plan_set_resolution(lm_plan *p, const double fwhm_vox[3], void *stream) {
     // the plan's own g = G^T 1 becomes the sensitivity of G B, B G^T 1 (B is
     // symmetric), and T follows it
     if (!p->g0) {
-      if (int rc = dalloc(p, &p->g0, (size_t)E)) return rc;
+      lmh::Slab image;
+      image.add(&p->g0, E);
+      if (int rc = dalloc(p, image)) return rc;
       LM_TRY_HIP(hipMemcpyAsync(p->g0, p->gimg, E * sizeof(float), hipMemcpyDeviceToDevice, st));
     }
     if (b.on) {
@@ -793,8 +791,9 @@ int lm_plan_set_prior_image(lm_plan *p, const float *v, double eta, void *stream
   hipStream_t st = lmh::as_stream(stream);
   p->last = st;
   if (!p->xi_dtv) {
-    if (int rc = dalloc(p, &p->xi_dtv, (size_t)(p->ne * p->ncomp))) return rc;
-    if (int rc = dalloc(p, &p->pd, (size_t)(p->ne * p->ncomp))) return rc;
+    lmh::Slab fields;
+    for (float **q : {&p->xi_dtv, &p->pd}) fields.add(q, p->ne * p->ncomp);
+    if (int rc = dalloc(p, fields)) return rc;
   }
   if (int rc = lmk::launch_dtv_field(p->G.n, p->lay, p->ncomp, p->ne, v, (float)eta, p->xi_dtv, st)) return rc;
   p->dtv = true;

@@ -199,22 +199,18 @@ int group_by_key(const unsigned *key, long long n, unsigned nb, unsigned *out, u
   unsigned *hi_tot = nullptr, *hi_off = nullptr, *hi_fill = nullptr, *chunk_off = nullptr, *tot = nullptr,
            *fill = nullptr, *tkey = nullptr;
   unsigned *tidx = nullptr;
-  auto release = [&]() {  // release errors are not reported
-    for (void *q : {(void *)hi_tot, (void *)hi_off, (void *)hi_fill, (void *)chunk_off, (void *)tot, (void *)fill,
-                    (void *)tkey, (void *)tidx})
-      if (q) (void)hipFreeAsync(q, st);
-  };
-  const size_t nn = (size_t)std::max<long long>(n, 1);
-  hipError_t e = hipMallocAsync((void **)&hi_tot, kRadix * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&hi_off, (kRadix + 1) * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&hi_fill, kRadix * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&chunk_off, (kRadix + 1) * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&tot, nbk * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&fill, nbk * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&tkey, nn * sizeof(unsigned), st);
-  if (e == hipSuccess) e = hipMallocAsync((void **)&tidx, nn * sizeof(unsigned), st);
+  lmh::Slab temporaries;
+  temporaries.add(&hi_tot, kRadix);
+  temporaries.add(&hi_off, kRadix + 1);
+  temporaries.add(&hi_fill, kRadix);
+  temporaries.add(&chunk_off, kRadix + 1);
+  temporaries.add(&tot, nbk);
+  temporaries.add(&fill, nbk);
+  temporaries.add(&tkey, n);
+  temporaries.add(&tidx, n);
+  void *tmp = nullptr;
+  hipError_t e = temporaries.alloc(st, &tmp);
   if (e != hipSuccess) {
-    release();
     (void)hipGetLastError();
     if (e == hipErrorOutOfMemory) return LM_ENOMEM;
     lmh::set_error("grouping temporaries: %s", hipGetErrorString(e));
@@ -242,7 +238,7 @@ int group_by_key(const unsigned *key, long long n, unsigned nb, unsigned *out, u
   } else if (e == hipSuccess) {
     e = hipMemsetAsync(off, 0, ((size_t)nb + 1) * sizeof(unsigned), st);
   }
-  release();
+  (void)hipFreeAsync(tmp, st);  // a release error is not reported
   if (e != hipSuccess) {
     lmh::set_error("grouping: %s", hipGetErrorString(e));
     return LM_EHIP;

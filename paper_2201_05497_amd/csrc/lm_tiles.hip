@@ -432,26 +432,22 @@ int build_tiles(const GeomDev &g, const int4 *rec, const std::vector<int> &off, 
   int *ord = nullptr;
   SegRay *rays = nullptr;
   float *cf = nullptr;
-  std::vector<void *> tmp;
+  void *tmp = nullptr, *kept = nullptr;  // allocations of the temporaries and of what is kept beside soff
   auto drop = [&](bool keep_error) {
-    for (void *q : tmp) (void)hipFreeAsync(q, st);
-    for (void *q : {(void *)soff, (void *)seg, (void *)ord, (void *)rays, (void *)cf})
+    for (void *q : {tmp, (void *)soff, kept})
       if (q) (void)hipFreeAsync(q, st);
     if (!keep_error) (void)hipGetLastError();
   };
-  auto get = [&](auto **ptr, size_t bytes, bool temporary) {
-    const hipError_t e = hipMallocAsync((void **)ptr, std::max<size_t>(bytes, 1), st);
-    if (e == hipSuccess && temporary) tmp.push_back(*ptr);
-    if (e != hipSuccess) *ptr = nullptr;
-    return e;
-  };
-  hipError_t e = get(&cnt, nbin * sizeof(unsigned), true);
-  if (e == hipSuccess) e = get(&bsum, nblk * sizeof(unsigned long long), true);
-  if (e == hipSuccess) e = get(&boff, (nblk + 1) * sizeof(long long), true);
-  if (e == hipSuccess) e = get(&load, tg.ntiles * sizeof(unsigned long long), true);
-  if (e == hipSuccess) e = get(&sub, (nsub + 1) * sizeof(long long), true);
-  if (e == hipSuccess) e = get(&first, (nsub + 1) * sizeof(long long), true);
-  if (e == hipSuccess) e = get(&soff, (nbin + 1) * sizeof(long long), false);
+  lmh::Slab temporaries;
+  temporaries.add(&cnt, nbin);
+  temporaries.add(&bsum, nblk);
+  temporaries.add(&boff, nblk + 1);
+  temporaries.add(&load, tg.ntiles);
+  temporaries.add(&sub, nsub + 1);
+  temporaries.add(&first, nsub + 1);
+  hipError_t e = temporaries.alloc(st, &tmp);
+  if (e == hipSuccess && (e = hipMallocAsync((void **)&soff, (nbin + 1) * sizeof(long long), st)) != hipSuccess)
+    soff = nullptr;
   if (e != hipSuccess) {
     drop(false);
     return LM_OK;  // no room: the per-event path
@@ -499,10 +495,12 @@ int build_tiles(const GeomDev &g, const int4 *rec, const std::vector<int> &off, 
   std::vector<int> order(tg.ntiles);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return hload[a] > hload[b]; });
-  e = get(&seg, total * sizeof(unsigned), false);
-  if (e == hipSuccess) e = get(&ord, tg.ntiles * sizeof(int), false);
-  if (e == hipSuccess) e = get(&rays, nlargest * sizeof(SegRay), false);
-  if (e == hipSuccess) e = get(&cf, nlargest * sizeof(float), false);
+  lmh::Slab lists;
+  lists.add(&seg, total);
+  lists.add(&ord, tg.ntiles);
+  lists.add(&rays, nlargest);
+  lists.add(&cf, nlargest);
+  e = lists.alloc(st, &kept);
   if (e != hipSuccess) {
     drop(false);
     return LM_OK;  // no room for the segments: the per-event path
@@ -516,8 +514,8 @@ int build_tiles(const GeomDev &g, const int4 *rec, const std::vector<int> &off, 
   if ((e = hipGetLastError()) != hipSuccess) return fail(e);
   // the host order vector dies with this call
   if ((e = hipStreamSynchronize(st)) != hipSuccess) return fail(e);
-  for (void *q : tmp) (void)hipFreeAsync(q, st);
-  for (void *q : {(void *)soff, (void *)seg, (void *)ord, (void *)rays, (void *)cf}) owned.push_back(q);
+  (void)hipFreeAsync(tmp, st);
+  for (void *q : {(void *)soff, kept}) owned.push_back(q);
   // TOF weights from a table where the geometry has one
   TofTab tt{};
   float4 *tab = nullptr;
