@@ -621,7 +621,9 @@ __device__ __forceinline__ float2 fwd_sample(const GeomDev &g, ImageBuf x, const
 }
 
 // The planes of one event for lane gl of its group of LPE: m0 + j for j = gl -
-// (brick offset of m0), + LPE, ...  Returns the lane's weighted sum.
+// (offset of m0 within a brick), + LPE, ..., the same in any layout, so that
+// a bricked and a row-major image give the same bits.  Returns the lane's
+// weighted sum.
 template <bool TOF, int LPE>
 __device__ __forceinline__ float fwd_walk(const GeomDev &g, const float *__restrict__ img, const RayPack &pk,
                                           float D, int gl) {
@@ -631,7 +633,7 @@ __device__ __forceinline__ float fwd_walk(const GeomDev &g, const float *__restr
   const int b1 = (a == 0) ? 1 : 0, b2 = (a == 2) ? 1 : 2;
   const AxisTerm ta = axis_term(g.lay, a), t1 = axis_term(g.lay, b1), t2 = axis_term(g.lay, b2);
   const int n1 = sel3(b1, g.n[0], g.n[1], g.n[2]), n2 = sel3(b2, g.n[0], g.n[1], g.n[2]);
-  int j = gl - (m0 & ta.mask & kMaxBrickOffset);
+  int j = gl - (m0 & kMaxBrickOffset);
   // plane term of m0 + j (>= 0: the offset stays inside m0's brick),
   // advanced by whole bricks, LPE planes at a time
   int fa = axis_index(ta, m0 + j);

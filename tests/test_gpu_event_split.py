@@ -1,8 +1,9 @@
 """GPU parity of the kernels whose split depends on the length of the list or
 on the number of image tiles, at the edges of their ranges, against the FP64
 oracle: the forward projection (2, 8, 16 or 64 events per wavefront) and the
-data update of a plan (512 or 256 threads per 8x8x8 tile).  Tolerances as
-for every projection (1e-5) and iterate (1e-4)."""
+data update of a plan (512 or 256 threads per 8x8x8 tile), and the projector
+pair of lists short enough to work on the caller's image.  Tolerances as for
+every projection (1e-5), back projection and iterate (1e-4)."""
 import numpy as np
 import pytest
 import torch
@@ -14,6 +15,7 @@ from tests.helpers import img_err, proj_err, report, smooth_image
 pytestmark = pytest.mark.gpu
 
 PROJ_TOL = 1e-5
+BACK_TOL = 1e-4
 ITER_TOL = 1e-4
 
 
@@ -54,6 +56,30 @@ def test_forward_at_the_edges_of_its_splits(P, n, h, tof):
         emax, _ = proj_err(got[idx], oracle.fwd(Go, x, ev[idx]))
         report(f"forward split {n} tof={tof}", events=m, err=emax)
         assert emax <= PROJ_TOL
+
+
+@pytest.mark.parametrize("n,h,tof", [
+    ((101, 97, 3), (1.0, 1.3, 1.7), True),
+    ((300, 299, 1), (1.0, 1.0, 1.0), False),
+])
+def test_projector_pair_of_short_lists(P, n, h, tof):
+    """Lists short enough to work on the caller's image (by events x planes)
+    and lists just beyond, into an image that holds values."""
+    p, Gg, Go = _geometry(P, n, h, tof)
+    ev = lmsynth.random_events(p, 32767, seed=67, min_sep=1)
+    x = smooth_image(Go.shape, 68)
+    xd, evd = torch.as_tensor(x, dtype=torch.float32, device="cuda"), Gg.events(ev)
+    v = np.random.default_rng(69).uniform(-1, 1, len(ev)).astype(np.float32)
+    vd = torch.as_tensor(v, device="cuda")
+    for m in (1, 65, 3000, 6000, 9000, 32767):
+        got = P.lm_fwd(Gg, xd, evd[:m].contiguous()).cpu().numpy()
+        emax, _ = proj_err(got, oracle.fwd(Go, x, ev[:m]))
+        img = torch.full(Gg.shape, 0.5, device="cuda")
+        P.lm_back(Gg, vd[:m].contiguous(), evd[:m].contiguous(), img)
+        want = oracle.back(Go, v[:m].astype(np.float64), ev[:m]) + 0.5
+        e = img_err(img.cpu().numpy(), want)
+        report(f"short lists {n} tof={tof}", events=m, fwd=emax, back=e)
+        assert emax <= PROJ_TOL and e <= BACK_TOL
 
 
 @pytest.mark.parametrize("n,h,tof", [
