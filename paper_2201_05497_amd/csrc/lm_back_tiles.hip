@@ -59,7 +59,8 @@ __device__ void scatter_event(const GeomDev &g, const Ray &r, float c, float *im
 __global__ __launch_bounds__(kBinBlock) void k_list_count(GeomDev g, TileGeom tg, int maxp, const int16_t *ev,
                                                           const int4 *rec, const float *__restrict__ v, int n,
                                                           int chunk, SegRay *__restrict__ rays,
-                                                          float *__restrict__ val, unsigned *tot, float *img) {
+                                                          float *__restrict__ val, unsigned *tot,
+                                                          unsigned *__restrict__ base, float *img) {
   extern __shared__ unsigned h[];
   for (int t = threadIdx.x; t < tg.ntiles; t += kBinBlock) h[t] = 0u;
   __syncthreads();
@@ -89,8 +90,10 @@ __global__ __launch_bounds__(kBinBlock) void k_list_count(GeomDev g, TileGeom tg
     for_each_segment<kTL>(g, s, tg, [&](int t) { atomicAdd(&h[t], 1u); });
   }
   __syncthreads();
+  // the workgroup's place within each tile is what the tile's count was
+  base += (long long)tg.ntiles * blockIdx.x;
   for (int t = threadIdx.x; t < tg.ntiles; t += kBinBlock)
-    if (h[t]) atomicAdd(tot + t, h[t]);
+    if (h[t]) base[t] = atomicAdd(tot + t, h[t]);
 }
 
 // First segment of every tile (off, ntiles + 1 entries) and the work items:
@@ -141,20 +144,17 @@ __global__ __launch_bounds__(1024) void k_list_items(const unsigned *__restrict_
 }
 
 // Lists the events of every tile: seg[off[t] ..] of tile t, each workgroup
-// in a range of its own (reserved with one atomic on fill[t]).
+// in the range that it reserved when counting (tiles that it did not count
+// have none, and are not met here).
 __global__ __launch_bounds__(kBinBlock) void k_list_place(GeomDev g, TileGeom tg, const SegRay *__restrict__ rays,
                                                           int n, int chunk, const unsigned *__restrict__ off,
-                                                          unsigned *fill, unsigned *__restrict__ seg) {
+                                                          const unsigned *__restrict__ base,
+                                                          unsigned *__restrict__ seg) {
   extern __shared__ unsigned h[];
-  for (int t = threadIdx.x; t < tg.ntiles; t += kBinBlock) h[t] = 0u;
+  base += (long long)tg.ntiles * blockIdx.x;
+  for (int t = threadIdx.x; t < tg.ntiles; t += kBinBlock) h[t] = off[t] + base[t];
   __syncthreads();
   const int e0 = blockIdx.x * chunk, e1 = min(n, e0 + chunk);
-  for (int e = e0 + threadIdx.x; e < e1; e += kBinBlock)
-    for_each_segment<kTL>(g, rays[e], tg, [&](int t) { atomicAdd(&h[t], 1u); });
-  __syncthreads();
-  for (int t = threadIdx.x; t < tg.ntiles; t += kBinBlock)
-    if (h[t]) h[t] = off[t] + atomicAdd(fill + t, h[t]);
-  __syncthreads();
   for (int e = e0 + threadIdx.x; e < e1; e += kBinBlock)
     for_each_segment<kTL>(g, rays[e], tg, [&](int t) { seg[atomicAdd(&h[t], 1u)] = (unsigned)e; });
 }
@@ -258,25 +258,34 @@ int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const
   const long long batch = std::min(std::min(n, 1LL << 30), kListSegBytes / (4 * pe));
   if (batch < kMinListEvents) return LM_OK;  // very unequal voxel sides: too many tiles per event to plan for
   const long long items = batch * pe / kItemMin + tg.ntiles;
-  // one allocation: rays, items, segment numbers, values, tot and fill, off, nitems
-  const size_t b_rays = (size_t)batch * sizeof(SegRay), b_items = (size_t)items * sizeof(uint2),
-               b_seg = (size_t)(batch * pe) * sizeof(unsigned), b_val = (size_t)batch * sizeof(float),
-               b_tile = (size_t)(3 * tg.ntiles + 3) * sizeof(unsigned);
-  char *tmp = nullptr;
+  // events of a binning workgroup: enough workgroups to fill the chip, few
+  // enough that their histograms (cleared, added and kept per workgroup)
+  // stay a small part
+  const int chunk =
+      (int)std::min<long long>(4096, ((batch + 1023) / 1024 + kBinBlock - 1) / kBinBlock * kBinBlock);
+  const long long rows = (batch + chunk - 1) / chunk;
+  SegRay *rays = nullptr;
+  uint2 *item = nullptr;
+  unsigned *seg = nullptr, *tot = nullptr, *off = nullptr, *nitems = nullptr, *base = nullptr;
+  float *val = nullptr;
+  lmh::Slab arrays;
+  arrays.add(&rays, batch);
+  arrays.add(&item, items);
+  arrays.add(&seg, batch * pe);
+  arrays.add(&val, batch);
+  arrays.add(&tot, tg.ntiles);
+  arrays.add(&off, tg.ntiles + 1);
+  arrays.add(&nitems, 2);
+  arrays.add(&base, rows * tg.ntiles);
+  void *tmp = nullptr;
   {
-    const hipError_t e = hipMallocAsync((void **)&tmp, b_rays + b_items + b_seg + b_val + b_tile, st);
+    const hipError_t e = arrays.alloc(st, &tmp);
     if (e == hipErrorOutOfMemory) {
       (void)hipGetLastError();
       return LM_OK;  // the per-event path needs no temporaries
     }
     LM_TRY_HIP(e);
   }
-  SegRay *rays = (SegRay *)tmp;
-  uint2 *item = (uint2 *)(tmp + b_rays);
-  unsigned *seg = (unsigned *)(tmp + b_rays + b_items);
-  float *val = (float *)(tmp + b_rays + b_items + b_seg);
-  unsigned *tot = (unsigned *)(tmp + b_rays + b_items + b_seg + b_val), *fill = tot + tg.ntiles,
-           *off = fill + tg.ntiles, *nitems = off + tg.ntiles + 1;
   TofTab tt{};
   float4 *tab = nullptr;
   int rc = build_tof_table(g, tt, &tab, st);
@@ -284,18 +293,15 @@ int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const
   hipError_t e = hipSuccess;
   for (long long o = 0; rc == LM_OK && e == hipSuccess && o < n; o += batch) {
     const int m = (int)std::min(batch, n - o);
-    // enough workgroups to fill the chip, few enough that their histograms
-    // (cleared, added and reserved per workgroup) stay a small part
-    const int chunk = (int)std::min<long long>(4096, ((m + 1023) / 1024 + kBinBlock - 1) / kBinBlock * kBinBlock);
     const unsigned nb = (unsigned)((m + chunk - 1) / chunk);
     const int16_t *evo = ev ? ev + 5 * o : nullptr;
     const int4 *reco = ev ? nullptr : rec + o;
-    hipLaunchKernelGGL(k_zero_u32, dim3(std::min(64, (2 * tg.ntiles + 255) / 256)), dim3(256), 0, st, tot,
-                       2LL * tg.ntiles);
+    hipLaunchKernelGGL(k_zero_u32, dim3(std::min(64, (tg.ntiles + 255) / 256)), dim3(256), 0, st, tot,
+                       (long long)tg.ntiles);
     hipLaunchKernelGGL(k_list_count, dim3(nb), dim3(kBinBlock), lds, st, g, tg, maxp, evo, reco, v + o, m, chunk,
-                       rays, val, tot, img);
+                       rays, val, tot, base, img);
     hipLaunchKernelGGL(k_list_items, dim3(1), dim3(1024), 0, st, tot, tg.ntiles, off, item, nitems);
-    hipLaunchKernelGGL(k_list_place, dim3(nb), dim3(kBinBlock), lds, st, g, tg, rays, m, chunk, off, fill, seg);
+    hipLaunchKernelGGL(k_list_place, dim3(nb), dim3(kBinBlock), lds, st, g, tg, rays, m, chunk, off, base, seg);
 #define LM_LB(TM_)                                                                                                  \
   hipLaunchKernelGGL((k_list_back<TM_>), dim3(kBackGrid), dim3(kBackBlock), tlds, st, g, tg, off, item, nitems, seg, \
                      rays, val, tt, tab, img)
