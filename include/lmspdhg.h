@@ -81,8 +81,8 @@ const char *lm_last_error(void);
 /* ---------------------------------------------------------------- projector */
 
 /* Images passed to the projector calls are row-major float[nz][ny][nx]
- * device arrays.  Each call copies the image into a temporary in the
- * library's 4x4x4-voxel brick layout (stream-ordered hipMallocAsync on
+ * device arrays.  A call with more than a short list copies the image into a
+ * temporary in the library's 4x4x4-voxel brick layout (stream-ordered hipMallocAsync on
  * `stream`, freed stream-ordered before the call returns; LM_ENOMEM if it
  * cannot be allocated), runs on the copy, and for lm_back / lm_sens writes
  * the result back.  All work is queued on `stream` (NULL: the default
@@ -90,14 +90,19 @@ const char *lm_last_error(void);
 
 /* Listmode forward projection (Eq. lmop): out[e] = (P^LM x)_e for the n
  * events ev[n][5] in the caller's order.  x: image; out: float[n].  Events
- * that are out of range get out[e] = 0.  On a cylindrical scanner (crystal c
- * of ring r at (x_c, y_c, z_r), z increasing with r; decided by a kernel that
- * reads the crystal table) a list of at least 64 events per transaxial
- * crystal pair and fewer than 2^31 events is projected by
- * transaxial line after a counting sort on the device: 24 more bytes per
- * event of stream-ordered temporary memory (without room for it the events
- * are projected in their own order).  The result is the same up to float32
- * rounding in either order.  The call never synchronises the stream. */
+ * that are out of range get out[e] = 0.  Short lists read x as it is.  Long
+ * lists (2^19 events and more on images beyond 16 MB, 4 MB without TOF) are
+ * projected in a spatial order that the call makes on the device: 22 bytes
+ * per event, of up to 2^26 events at a time, and a second image of
+ * stream-ordered temporary memory (without room for it the events are
+ * projected in their own order); the result is the same, bit for bit.
+ * Without TOF or on a single slice, on a cylindrical scanner (crystal c of
+ * ring r at (x_c, y_c, z_r), z increasing with r; decided by a kernel that
+ * reads the crystal table), a list of at least 64 events per transaxial
+ * crystal pair and fewer than 2^31 events is projected by transaxial line
+ * after a counting sort on the device (24 bytes per event); the result is
+ * then the same up to float32 rounding.  The call never synchronises the
+ * stream. */
 int lm_fwd(const lm_geom *G, const float *x, const int16_t *ev, int64_t n, float *out,
            void *stream);
 

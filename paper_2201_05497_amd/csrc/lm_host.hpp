@@ -187,6 +187,20 @@ struct BrickImage {
     }
     return LM_OK;
   }
+  // A pair image instead (see pair_layout), without room for it nothing.
+  int alloc_pairs(lmk::GeomDev &g, hipStream_t s) {
+    const lmk::Layout L = lmk::pair_layout(lmh::brick_layout(g.n), g.n[2]);
+    st = s;
+    const hipError_t e = hipMallocAsync((void **)&p, (size_t)lmk::layout_size(L) * 2 * sizeof(float), s);
+    if (e == hipErrorOutOfMemory) {
+      p = nullptr;
+      (void)hipGetLastError();
+      return LM_OK;
+    }
+    LM_TRY_HIP(e);
+    g.lay = L;
+    return LM_OK;
+  }
   ~BrickImage() {
     if (p) (void)hipFreeAsync(p, st);  // a release error has no caller to go to
   }

@@ -489,6 +489,16 @@ __global__ __launch_bounds__(kBlock) void k_to_layout(const float *__restrict__ 
   for (int c = 0; c < ncomp; ++c) dst[c * ne + q] = src[c * nv + v];
 }
 
+// Row-major image -> pair image in layout L (see pair_layout).
+__global__ __launch_bounds__(kBlock) void k_to_pairs(const float *__restrict__ src, float2 *__restrict__ dst,
+                                                     lmk::Layout L, int nx, int ny, int nz) {
+  const long long nxy = (long long)nx * ny;
+  const long long v = (long long)blockIdx.x * kBlock + threadIdx.x;
+  if (v >= nxy * (nz + 1)) return;
+  const int i = (int)(v % nx), j = (int)((v / nx) % ny), k = (int)(v / nxy);
+  dst[lmk::vidx(L, i, j, k)] = make_float2(k > 0 ? src[v - nxy] : 0.0f, k < nz ? src[v] : 0.0f);
+}
+
 // Layout L -> row-major image, ncomp components.
 __global__ __launch_bounds__(kBlock) void k_from_layout(const float *__restrict__ src, float *__restrict__ dst,
                                                         lmk::Layout L, int nx, int ny, int nz, long long ne,
@@ -587,6 +597,13 @@ int launch_tv_fused(const int n[3], const Layout &L, int ncomp, const float *x, 
     lmh::set_error("prior update: the image layout must be 4x4x4 bricks (or 4x4x1 for one slice)");
     return LM_EINVAL;
   }
+  LM_TRY_HIP(hipGetLastError());
+  return LM_OK;
+}
+
+int launch_to_pairs(const int n[3], const Layout &L, const float *src, float *dst, hipStream_t st) {
+  const long long nv = (long long)n[0] * n[1] * (n[2] + 1);
+  hipLaunchKernelGGL(k_to_pairs, dim3(grid_for(nv)), dim3(kBlock), 0, st, src, (float2 *)dst, L, n[0], n[1], n[2]);
   LM_TRY_HIP(hipGetLastError());
   return LM_OK;
 }

@@ -28,7 +28,9 @@ int launch_tv_fused(const int n[3], const Layout &L, int ncomp, const float *x, 
 bool prior_march_ok(const Layout &L, int ncomp);
 
 // Conversions between the caller's row-major images (ncomp components of
-// n[0] n[1] n[2] elements) and layout L (ncomp components of layout_size(L)).
+// n[0] n[1] n[2] elements) and layout L (ncomp components of layout_size(L);
+// to_pairs: a pair image, whose layout pair_layout gives).
+int launch_to_pairs(const int n[3], const Layout &L, const float *src, float *dst, hipStream_t st);
 int launch_to_layout(const int n[3], const Layout &L, int ncomp, const float *src, float *dst, hipStream_t st);
 int launch_from_layout(const int n[3], const Layout &L, int ncomp, const float *src, float *dst, hipStream_t st);
 

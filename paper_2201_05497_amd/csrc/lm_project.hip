@@ -17,6 +17,7 @@
 #include "lm_device.hpp"
 #include "lm_host.hpp"
 #include "lm_image.hpp"
+#include "lm_order.hpp"
 #include "lm_segs.hpp"
 
 using namespace lmk;
@@ -52,6 +53,17 @@ struct PlanEvents {
   }
   __device__ __forceinline__ long long slot(long long e) const { return e; }
 };
+// The caller's events in spatial order.
+struct OrderedEvents {
+  static constexpr bool kXcdOrder = false;
+  const OrderedEvent *rec;
+  OrderedEvents offset(long long o) const { return OrderedEvents{rec + o}; }
+  __device__ __forceinline__ bool get(const GeomDev &g, long long e, int &id1, int &id2, int &k) const {
+    const OrderedEvent o = rec[e];
+    return decode_event(g, o.ev, id1, id2, k);
+  }
+  __device__ __forceinline__ long long slot(long long e) const { return e; }
+};
 struct SortedEvents {
   static constexpr bool kXcdOrder = true;
   const int16_t *ev;
@@ -79,8 +91,11 @@ constexpr long long kFwdLaunch = 1LL << 27;
 // samples lie on lines of their own, which the L1 serves at 1.4 lanes per
 // clock and CU, the rate this kernel reaches (2.7 ms for 1e7 events on
 // 200x200x96).  Tabulated TOF weights, 40 of 130 instructions per sample
-// fewer, took 3.0 ms.
-template <class Src, bool TOF, int LPE, int EPW>
+// fewer, took 3.0 ms.  PAIRS: x is a pair image, which halves the look-ups
+// of rays along x or y, but not the lines that it misses in the L2: 3.2 ms
+// in list order, 1.75 in spatial order (2.0 with the ordering), bound by
+// instruction issue.
+template <class Src, bool TOF, int LPE, int EPW, bool PAIRS>
 __global__ __launch_bounds__(kBlock) void k_fwd(GeomDev g, const int *skip, const float *__restrict__ x, Src src,
                                                 long long n, float *__restrict__ out) {
   constexpr int kGroups = 64 / LPE, kRounds = EPW / kGroups, kPerBlock = EPW * (kBlock / 64);
@@ -116,7 +131,15 @@ __global__ __launch_bounds__(kBlock) void k_fwd(GeomDev g, const int *skip, cons
   for (int round = 0; round < kRounds; ++round) {
     const RayPack pk = wrays[kGroups * round + grp];
     float acc = 0.0f;
-    if (pk.p.y > 0) acc = fwd_walk<TOF, LPE>(g, x, pk, D, gl);
+    if constexpr (PAIRS) {
+      const bool along_z = __any(pk.p.y > 0 && pk.p.z == 2);
+      if (pk.p.y > 0) {
+        if (!along_z) acc = fwd_walk<TOF, LPE, kPairs>(g, x, pk, D, gl);
+        else acc = fwd_walk<TOF, LPE, kPairsAnyAxis>(g, x, pk, D, gl);
+      }
+    } else {
+      if (pk.p.y > 0) acc = fwd_walk<TOF, LPE>(g, x, pk, D, gl);
+    }
     acc = group_sum<LPE>(acc);
     // lanes kGroups round .. take the sums of the groups
     const float got = __shfl(acc, LPE * (lane % kGroups));
@@ -326,7 +349,7 @@ int max_planes(const lmk::GeomDev &g, int mode) {
 
 namespace lmk {
 
-template <class Src, int LPE, int EPW>
+template <class Src, int LPE, int EPW, bool PAIRS>
 static int fwd_launch(const GeomDev &g, const float *x, Src src, long long n, float *out, hipStream_t st,
                       const int *skip) {
   constexpr int kPerBlock = EPW * (kBlock / 64);
@@ -337,10 +360,10 @@ static int fwd_launch(const GeomDev &g, const float *x, Src src, long long n, fl
     // sorted sources write out[order[e]]: out is the whole list's
     float *o_out = Src::kXcdOrder ? out : out + o;
     if (g.tof_on)
-      hipLaunchKernelGGL((k_fwd<Src, true, LPE, EPW>), dim3(nb), dim3(kBlock), 0, st, g, skip, x, src.offset(o), m,
+      hipLaunchKernelGGL((k_fwd<Src, true, LPE, EPW, PAIRS>), dim3(nb), dim3(kBlock), 0, st, g, skip, x, src.offset(o), m,
                          o_out);
     else
-      hipLaunchKernelGGL((k_fwd<Src, false, LPE, EPW>), dim3(nb), dim3(kBlock), 0, st, g, skip, x, src.offset(o), m,
+      hipLaunchKernelGGL((k_fwd<Src, false, LPE, EPW, PAIRS>), dim3(nb), dim3(kBlock), 0, st, g, skip, x, src.offset(o), m,
                          o_out);
     LM_TRY_HIP(hipGetLastError());
   }
@@ -353,14 +376,14 @@ static int fwd_launch(const GeomDev &g, const float *x, Src src, long long n, fl
 // half a wavefront takes each event, which shortens the chain of its
 // samples.  3571 events of the single-slice problem: 41 -> 6.4 us in the
 // kernel.
-template <class Src>
+template <class Src, bool PAIRS = false>
 static int fwd_impl(const GeomDev &g, const float *x, Src src, long long n, float *out, hipStream_t st,
                     const int *skip = nullptr) {
   if (n == 0) return LM_OK;
-  if (Src::kXcdOrder || n >= (1 << 19)) return fwd_launch<Src, 8, 64>(g, x, src, n, out, st, skip);
-  if (n >= (1 << 16)) return fwd_launch<Src, 8, 16>(g, x, src, n, out, st, skip);
-  if (n >= (1 << 14)) return fwd_launch<Src, 8, 8>(g, x, src, n, out, st, skip);
-  return fwd_launch<Src, 32, 2>(g, x, src, n, out, st, skip);
+  if (Src::kXcdOrder || n >= (1 << 19)) return fwd_launch<Src, 8, 64, PAIRS>(g, x, src, n, out, st, skip);
+  if (n >= (1 << 16)) return fwd_launch<Src, 8, 16, PAIRS>(g, x, src, n, out, st, skip);
+  if (n >= (1 << 14)) return fwd_launch<Src, 8, 8, PAIRS>(g, x, src, n, out, st, skip);
+  return fwd_launch<Src, 32, 2, PAIRS>(g, x, src, n, out, st, skip);
 }
 
 // Grid of the grid-stride scattering kernels: enough wavefronts to fill the
@@ -514,6 +537,56 @@ static bool short_list(const GeomDev &g, long long n, long long samples) {
 }
 constexpr long long kShortFwd = 1LL << 22, kShortBack = 1LL << 21;
 
+// Lists projected from the pair image (twice the memory), and in spatial
+// order (which costs some 60 us and 20 ns per event).  Without the order pairs
+// pay while the L2 of an XCD holds a good part of them, beyond that only with
+// it.  Wall time per call in us, bricks / pairs / pairs in order (672 crystals
+// x 96 rings, emissions of a phantom; TOF: 90 planes per event):
+//   128x128x48, TOF      1e5  53 / 51 / 106    1e6  231 / 190 / 242     8e6  1380 / 1086 / 1209
+//   128x128x48, no TOF   1e5  85 / 62 / 112    1e6  536 / 337 / 335     8e6  3815 / 2375 / 1832
+//   160x160x64, TOF      1e5  64 / 53 / 111    1e6  280 / 224 / 272     8e6  1724 / 1290 / 1466
+//   200x200x96, TOF      3e5  135 / 126 / 172  1e6  331 / 351 / 316     8e6  2154 / 2571 / 1689
+//   200x200x96, no TOF   3e5  359 / 370 / 411  1e6  1119 / 1174 / 1024  8e6  9002 / 9299 / 5615
+//   300x300x96, TOF      3e5  234 / 287 / 234  1e6  653 / 680 / 578     8e6  4738 / 4420 / 2403
+constexpr long long kPairsAlone = 16LL << 20;  // bytes
+static long long pair_bytes(const GeomDev &g) { return 8LL * g.n[0] * g.n[1] * (g.n[2] + 1); }
+static bool order_pays(const GeomDev &g, long long n) {
+  return g.n[2] > 1 && order_possible(g) && n >= (1 << 19) && pair_bytes(g) > (g.tof_on ? kPairsAlone : 4LL << 20) &&
+         n * lmh::max_planes(g, W_BIN) >= 16 * lmh::nvox_of(g.n);
+}
+static bool pairs_pay(const GeomDev &g, long long n) {
+  return g.n[2] > 1 && pair_bytes(g) <= kPairsAlone && n * lmh::max_planes(g, W_BIN) >= 4 * lmh::nvox_of(g.n);
+}
+
+// Forward projection from a pair image in spatial order, in equal pieces of
+// up to 2^26 events (equal, so that each is projected like a long list);
+// queued is false, with nothing enqueued, without room for the order.
+constexpr long long kOrderPiece = 1LL << 26;
+static int fwd_ordered(const GeomDev &g, const float *pairs, const int16_t *ev, long long n, float *out,
+                       hipStream_t st, bool &queued) {
+  const long long pieces = (n + kOrderPiece - 1) / kOrderPiece, piece = (n + pieces - 1) / pieces;
+  EventOrder o;
+  lmh::Slab arrays;
+  lmk::add_order(arrays, piece, o);
+  void *tmp = nullptr;
+  const hipError_t e = arrays.alloc(st, &tmp);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    return LM_OK;
+  }
+  LM_TRY_HIP(e);
+  int rc = LM_OK;
+  for (long long a = 0; rc == LM_OK && a < n; a += piece) {
+    const long long m = std::min(piece, n - a);
+    rc = lmk::launch_order(g, ev + 5 * a, m, o, st);
+    if (rc == LM_OK) rc = fwd_impl<OrderedEvents, true>(g, pairs, OrderedEvents{o.rec}, m, o.val, st);
+    if (rc == LM_OK) rc = lmk::launch_order_back(o, m, out + a, st);
+  }
+  (void)hipFreeAsync(tmp, st);  // a release error has no caller to go to
+  queued = true;
+  return rc;
+}
+
 // --------------------------------------------------------------------------
 // C ABI
 
@@ -528,17 +601,31 @@ int lm_fwd(const lm_geom *G, const float *x, const int16_t *ev, int64_t n, float
   if (n == 0) return LM_OK;
   hipStream_t st = lmh::as_stream(stream);
   if (short_list(g, n, kShortFwd)) return launch_fwd(g, x, ev, n, out, st);
-  lmh::BrickImage b;
-  if (int rc = b.alloc(g, st)) return rc;
-  if (int rc = lmk::launch_to_layout(g.n, g.lay, 1, x, b.p, st)) return rc;
-  // a long list is sorted by transaxial crystal pair and projected line by
-  // line on a cylindrical scanner, else per event in the sorted order (so
-  // that the events of a line share cache lines)
+  // a long list without TOF, or of a single slice, is sorted by transaxial
+  // crystal pair and projected line by line on a cylindrical scanner, else
+  // per event in the sorted order (so that the events of a line share cache
+  // lines); with TOF the spatial order is faster at any length (128 crystals x
+  // 16 rings on 200x200x96, 8e6 events: 2190 us by line, 1703 in order)
   unsigned *order = nullptr, *off = nullptr;
-  if (int rc = lmk::sort_events_by_line(g, ev, n, &order, &off, st)) return rc;
-  if (!order) return launch_fwd(g, b.p, ev, n, out, st);
-  int rc = LM_OK;
-  {
+  if (!g.tof_on || g.n[2] == 1)
+    if (int rc = lmk::sort_events_by_line(g, ev, n, &order, &off, st)) return rc;
+  lmh::BrickImage b;
+  const bool ordered = !order && order_pays(g, n);
+  if (ordered || (!order && pairs_pay(g, n))) {
+    if (int rc = b.alloc_pairs(g, st)) return rc;
+    if (b.p) {
+      if (int rc = lmk::launch_to_pairs(g.n, g.lay, x, b.p, st)) return rc;
+      bool queued = false;
+      if (ordered)
+        if (int rc = fwd_ordered(g, b.p, ev, n, out, st, queued)) return rc;
+      if (queued) return LM_OK;
+      return fwd_impl<CallerEvents, true>(g, b.p, CallerEvents{ev}, n, out, st);
+    }
+  }
+  int rc = b.alloc(g, st);
+  if (rc == LM_OK) rc = lmk::launch_to_layout(g.n, g.lay, 1, x, b.p, st);
+  if (!order) return rc ? rc : launch_fwd(g, b.p, ev, n, out, st);
+  if (rc == LM_OK) {
     DevFlag cyl;
     bool queued = false;
     if (lines_possible(g)) {
