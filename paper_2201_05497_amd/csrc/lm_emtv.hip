@@ -71,27 +71,29 @@ struct Dual {
   float *q[3];
 };
 
-// EM image z = x n bp / g (0 where g = 0), x <- z.  With beta > 0 also the
-// weights w = g / (beta x) (inf where x = 0), the start of the denoising (u =
-// ubar = z, with u in x; q = 0) and the smallest weight of each block in
-// part[blockIdx.x] (as float bits: non-negative floats order like their
-// bits).
+// EM image z = x n bp / g (0 where g = 0), x <- z; bp is in layout L.  With
+// beta > 0 also the weights w = g / (beta x) (inf where x = 0), the start of
+// the denoising (u = ubar = z, with u in x) and the smallest weight of each
+// block in part[blockIdx.x] (as float bits: non-negative floats order like
+// their bits).
 __global__ __launch_bounds__(kBlock) void k_em_image(float *__restrict__ x, const float *__restrict__ bp,
-                                                     const float *__restrict__ g, long long nv, float nsub,
-                                                     float beta, float *__restrict__ z, float *__restrict__ w,
-                                                     float *__restrict__ ubar, Dual q, unsigned *__restrict__ part) {
+                                                     lmk::Layout L, int nx, int ny, const float *__restrict__ g,
+                                                     long long nv, float nsub, float beta, float *__restrict__ z,
+                                                     float *__restrict__ w, float *__restrict__ ubar,
+                                                     unsigned *__restrict__ part) {
   __shared__ unsigned red[kBlock / 64];
   unsigned lo = kInfBits;
   for (long long j = (long long)blockIdx.x * kBlock + threadIdx.x; j < nv; j += (long long)gridDim.x * kBlock) {
     const float xj = x[j], gj = g[j];
-    const float zj = gj > 0.0f ? xj * nsub * bp[j] / gj : 0.0f;
+    const unsigned row = (unsigned)j / (unsigned)nx, k = row / (unsigned)ny;
+    const float b = bp[lmk::vidx(L, (int)((unsigned)j - row * nx), (int)(row - k * ny), (int)k)];
+    const float zj = gj > 0.0f ? xj * nsub * b / gj : 0.0f;
     x[j] = zj;
     if (beta > 0.0f) {
       const float wj = xj > 0.0f ? gj / (beta * xj) : INFINITY;
       z[j] = zj;
       w[j] = wj;
       ubar[j] = zj;
-      for (int c = 0; c < 3; ++c) q.q[c][j] = 0.0f;
       lo = min(lo, __float_as_uint(wj));
     }
   }
@@ -109,17 +111,19 @@ __global__ __launch_bounds__(kBlock) void k_em_image(float *__restrict__ x, cons
 // theta_k = 1 / sqrt(1 + 2 gam tau_k), tau_{k+1} = theta_k tau_k,
 // sigma_{k+1} = sigma_k / theta_k, with gam the smallest finite weight
 // (0 if every weight is infinite or the smallest is 0), reduced here from
-// the npart block minima.  One block of kBlock threads.
-__global__ __launch_bounds__(kBlock) void k_pd_schedule(const unsigned *__restrict__ part, int npart, double tau0,
-                                                        int iters, float4 *__restrict__ sched) {
-  __shared__ unsigned red[kBlock / 64];
+// the npart block minima.  One block.
+constexpr int kSchedBlock = 1024;
+__global__ __launch_bounds__(kSchedBlock) void k_pd_schedule(const unsigned *__restrict__ part, int npart,
+                                                             double tau0, int iters, float4 *__restrict__ sched) {
+  __shared__ unsigned red[kSchedBlock / 64];
   unsigned lo = kInfBits;
-  for (int i = threadIdx.x; i < npart; i += kBlock) lo = min(lo, part[i]);
+#pragma unroll 4
+  for (int i = threadIdx.x; i < npart; i += kSchedBlock) lo = min(lo, part[i]);
   for (int o = 32; o > 0; o >>= 1) lo = min(lo, (unsigned)__shfl_xor((int)lo, o));
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = lo;
   __syncthreads();
   if (threadIdx.x != 0) return;
-  for (int i = 1; i < kBlock / 64; ++i) lo = min(lo, red[i]);
+  for (int i = 1; i < kSchedBlock / 64; ++i) lo = min(lo, red[i]);
   const double gam = lo < kInfBits ? (double)__uint_as_float(lo) : 0.0;
   double tau = tau0, sigma = tau0;
   for (int k = 0; k < iters; ++k) {
@@ -217,7 +221,7 @@ __global__ __launch_bounds__(kBlock) void k_pd_march(const float *__restrict__ u
     qn[2] = a2 * r;
   };
   auto load_q = [&](bool ok, unsigned p, float (&v)[3]) {
-    for (int c = 0; c < 3; ++c) v[c] = ok ? q.q[c][p] : 0.0f;
+    for (int c = 0; c < 3; ++c) v[c] = ok && it > 0 ? q.q[c][p] : 0.0f;  // q = 0 at the start
   };
   float below = 0.0f;  // q+ along z of the plane below
   if (kz0 > 0) {
@@ -388,8 +392,8 @@ int lm_emtv(const lm_geom *G, const int16_t *ev, const float *s, int64_t n, int3
 
   Temps t(st);
   int16_t *evs = nullptr;
-  float *ss = nullptr, *qe = nullptr, *xb = nullptr, *bpb = nullptr, *bp = nullptr;
-  float *z = nullptr, *w = nullptr, *u = nullptr, *ubar = nullptr, *q3 = nullptr;
+  float *ss = nullptr, *qe = nullptr, *xb = nullptr, *bpb = nullptr;
+  float *z = nullptr, *w = nullptr, *u = nullptr, *ubar = nullptr, *ubar2 = nullptr, *q3 = nullptr;
   float4 *sched = nullptr;
   unsigned *part = nullptr;
   Dual qa{}, qb{};
@@ -399,9 +403,8 @@ int lm_emtv(const lm_geom *G, const int16_t *ev, const float *s, int64_t n, int3
   arrays.add(&ss, n);
   arrays.add(&qe, m_max);
   for (float **q : {&xb, &bpb}) arrays.add(q, nb);
-  arrays.add(&bp, nv);
   if (denoise) {
-    for (float **q : {&z, &w, &u, &ubar}) arrays.add(q, nv);
+    for (float **q : {&z, &w, &u, &ubar, &ubar2}) arrays.add(q, nv);
     arrays.add(&q3, 3 * nv);
     arrays.add(&part, img_grid);
     arrays.add(&sched, iters);
@@ -433,14 +436,13 @@ int lm_emtv(const lm_geom *G, const int16_t *ev, const float *s, int64_t n, int3
         LM_TRY_HIP(hipGetLastError());
         if (int rc = lmk::launch_back(gb, qe, evs + 5 * o, m, bpb, st)) return rc;
       }
-      if (int rc = lmk::launch_from_layout(gd.n, gb.lay, 1, bpb, bp, st)) return rc;
-      hipLaunchKernelGGL(k_em_image, dim3(img_grid), dim3(kBlock), 0, st, x, bp, g, nv, (float)n_subsets, beta, z,
-                         w, ubar, qa, part);
+      hipLaunchKernelGGL(k_em_image, dim3(img_grid), dim3(kBlock), 0, st, x, bpb, gb.lay, gd.n[0], gd.n[1], g, nv,
+                         (float)n_subsets, beta, z, w, ubar, part);
       LM_TRY_HIP(hipGetLastError());
       if (iters == 0) continue;
-      hipLaunchKernelGGL(k_pd_schedule, dim3(1), dim3(kBlock), 0, st, part, (int)img_grid, tau0, iters, sched);
+      hipLaunchKernelGGL(k_pd_schedule, dim3(1), dim3(kSchedBlock), 0, st, part, (int)img_grid, tau0, iters, sched);
       LM_TRY_HIP(hipGetLastError());
-      float *ua = ubar, *ub = bp;
+      float *ua = ubar, *ub = ubar2;
       for (int k = 0; k < iters; ++k) {
         if (int rc = launch_pd(ua, k % 2 ? qb : qa, k % 2 ? qa : qb, x, z, w, ub, gd.n, sched, k, st)) return rc;
         std::swap(ua, ub);
