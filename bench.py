@@ -86,10 +86,10 @@ SERVE_BUDGET = 96 << 30         # HBM bytes the server may hold
 BYTES_PER_VOXEL = {"primal": 16, "dual_image": 28, "tv": 44}
 BYTES_PER_EVENT = 16 + 4 + 4 + 4 + 4
 BYTES_PER_EVENT_PROJ = 10 + 4
-# One accelerated PDHG step of the EM-TV denoising, per voxel: the dual pass
-# reads ubar and q (4 + 12) and writes q (12); the primal pass reads u, z,
-# w and q (4 + 4 + 4 + 12) and writes u and ubar (8).
-BYTES_PER_VOXEL_PD = 28 + 32
+# One accelerated PDHG step of the EM-TV denoising, one pass per voxel:
+# reads ubar, q, u, z and w (4 + 12 + 4 + 4 + 4) and writes q, u and ubar
+# (12 + 4 + 4).
+BYTES_PER_VOXEL_PD = 48
 # A DTV prior update in 3D, one pass per voxel (the TV pass's bytes plus
 # xi): reads x, w, xi, z and T (4 + 12 + 12 + 4 + 4) and writes w, z and x
 # (12 + 4 + 4).
@@ -102,12 +102,12 @@ WARM_DENOISE = 20               # 20 accelerated PDHG steps per denoising
 # traffic below was measured.
 CSRC = os.path.join(HERE, "paper_2201_05497_amd", "csrc")
 KERNEL_SOURCES = {
-    "data_update": ["lm_tiles.hip", "lm_tiles.hpp", "lm_project.hip", "lm_device.hpp"],
+    "data_update": ["lm_tiles.hip", "lm_tiles.hpp", "lm_segs.hpp", "lm_project.hip", "lm_device.hpp"],
     "dual_image": ["lm_image.hip"],
     "tv": ["lm_image.hip", "lm_device.hpp"],
     "primal": ["lm_image.hip"],
-    "fwd": ["lm_project.hip", "lm_device.hpp", "lm_lines.hip", "lm_sort.hip", "lm_sort.hpp"],
-    "back": ["lm_project.hip", "lm_device.hpp", "lm_lines.hip", "lm_sort.hip", "lm_sort.hpp"],
+    "fwd": ["lm_project.hip", "lm_device.hpp", "lm_order.hip", "lm_order.hpp"],
+    "back": ["lm_back_tiles.hip", "lm_segs.hpp", "lm_device.hpp"],
 }
 
 # HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE and
@@ -116,25 +116,17 @@ KERNEL_SOURCES = {
 # kernel's sources at the time.  The summaries are under profiles/.
 PMC_TRAFFIC: dict = {
     # the data update by image tile: phase 1 (k_tile_fwd) + phase 2 (k_tile_back)
-    "data_update": {"fetch_bytes": 231500000, "write_bytes": 80000000, "sources": "96219cb1c080b05d",
+    "data_update": {"fetch_bytes": 153300000, "write_bytes": 32600000, "sources": "fa3b9aa7144636e9",
         "profile": "profiles/epoch_3d_200x200x96_hbm_traffic.txt"},
-    "tv": {"fetch_bytes": 106400000, "write_bytes": 77000000, "sources": "5157d7dc3cd01a2c",
+    "tv": {"fetch_bytes": 106300000, "write_bytes": 77000000, "sources": "8227de5c540cce7f",
         "profile": "profiles/epoch_3d_200x200x96_hbm_traffic.txt"},
-    "dual_image": {"fetch_bytes": 61408650, "write_bytes": 46080000, "sources": "5bbf6922e857d5c6",
-        "profile": "profiles/epoch_3d_200x200x96_hbm_traffic.txt"},
-    # one lm_fwd / lm_back call over the 5e8-event long frame: the counting
-    # sort and the line kernels
-    "fwd": {"fetch_bytes": 104600000000, "write_bytes": 52000000000, "sources": "cfd073d3f5ea28e3",
-        "profile": "profiles/pass_3d_300x300x96_counters.txt"},
-    "back": {"fetch_bytes": 95400000000, "write_bytes": 118500000000, "sources": "cfd073d3f5ea28e3",
-        "profile": "profiles/pass_3d_300x300x96_counters.txt"},
 }
 
 
 # VALU wavefront instructions per launch (rocprofv3 --pmc SQ_INSTS_VALU),
 # with the digest of the kernel's sources at the time.
 PMC_VALU: dict = {
-    "data_update": {"instr_per_launch": 33050000, "sources": "96219cb1c080b05d",
+    "data_update": {"instr_per_launch": 17520000, "sources": "fa3b9aa7144636e9",
         "profile": "profiles/epoch_3d_200x200x96_l2_atomics_valu.txt"},
 }
 
@@ -171,8 +163,8 @@ def traffic(cls: str):
 
 
 def binding(cls: str, us_per_launch: float) -> dict:
-    """The resource that bounds the data update by tile (it issues no global
-    atomics; its phase 2 is bound by its arithmetic): measured VALU
+    """The arithmetic of the data update by tile (it issues no global
+    atomics): measured VALU
     wavefront instructions per launch / live launch duration against the
     chip's issue rate."""
     out = {"kernel": cls, "resource": "VALU wavefront instructions", "unit": "instructions/s",
@@ -354,7 +346,7 @@ def epoch_leg(args, torch, P, lmsynth):
         du = kernels["data_update"]
         du["events_per_s"] = round(n_proj / n_data / (du["us_avg"] * 1e-6), 1)
         # a data update is two launches: the per-event pass (forward, dual
-        # prox and its back projection, or the tile records) and the pass
+        # prox and its back projection, or its ray and value) and the pass
         # over the image that takes the z / zbar / primal step (k_dual_image,
         # or the back projection by tile fused with that step); its
         # algorithmic bytes are the per-event lists and that image step
@@ -754,8 +746,7 @@ def serving_leg(torch, P, lmsynth, G3, g3, p3, n_req: int = SERVE_REQUESTS, max_
 def large_leg(args, torch, P, lmsynth, passes: int, warmup: int):
     """The long static frame: 5e8 events on the 300x300x96 image, presented
     sorted by dominant axis.  `warmup` untimed and `passes` timed lm_fwd +
-    lm_back passes over all events (lm_back takes its by-line path for such
-    a list), then one LM-SPDHG epoch (224 subsets) after a warm-up epoch."""
+    lm_back passes over all events, then one LM-SPDHG epoch (224 subsets) after a warm-up epoch."""
     dev = torch.device("cuda", 0)
     n_events = args.large_events or LARGE_EVENTS
     t0 = time.perf_counter()

@@ -1,6 +1,6 @@
 // The paths by transaxial line, for cylindrical scanners (crystal c of ring r
 // at (x_c, y_c, z_r)): the sensitivity image P^T 1, and lm_fwd of long event
-// lists after a counting sort by line.
+// lists without TOF, or of a single slice, after a counting sort by line.
 //
 // Every line of response between crystals c1 != c2 of any two rings has the
 // same transaxial projection, so when its dominant axis is transaxial it
