@@ -136,8 +136,9 @@ __device__ __forceinline__ TileLane<TE> tile_lane(int ox, int oy, int oz, int p)
   return t;
 }
 
-// Adds the sample of ray s on the lane's plane, with event value val (finite:
-// a corner of weight 0 then adds 0), where `on`.  The corner's place in the
+// Adds the sample of ray s on the lane's plane, with event value val, where
+// `on`.  A value that is not finite reaches the corners of the samples of TOF
+// weight above 0 (also corners of weight 0).  The corner's place in the
 // accumulators is computed in float (whole numbers below 2^24, exact): the
 // voxel coordinates are floats already and an integer product takes four
 // times as long.
@@ -160,12 +161,14 @@ __device__ __forceinline__ void add_sample(const GeomDev &g, const TileLane<TE> 
     float v = val;
     if constexpr (TM != kTofNone) {
       const float tc = fmaf(-fj, s.b.w, s.b.z);
+      float w;
       if constexpr (TM == kTofTable) {
-        v *= tof_weight_tab(tu, tab, tc);
+        w = tof_weight_tab(tu, tab, tc);
       } else {
         const float vh = fmaf(0.5f, D, tc);
-        v *= tof_weight(vh, vh - D, g.vclip, g.inv_norm);
+        w = tof_weight(vh, vh - D, g.vclip, g.inv_norm);
       }
+      v = w != 0.0f ? val * w : 0.0f;
     }
     const float d1 = x_dom ? 8.0f * S::Y : 8.0f, d2 = z_dom ? 8.0f * S::Y : 8.0f * S::Z;
     const int at = (int)fmaf(l1, d1, fmaf(l2, d2, sel3(a, t.ax, t.ay, t.az)));

@@ -283,7 +283,9 @@ __global__ __launch_bounds__(kBlock1) void k_tile_fwd(GeomDev g, int maxp, const
           w = tof_weight(vh, vh - D, g.vclip, g.inv_norm);
         }
       }
-      acc = fmaf(j >= 0 ? w : 0.0f, v, acc);
+      // the planes of the brick before the ray's first add nothing, whatever
+      // value they hold
+      acc = fmaf(w, j >= 0 ? v : 0.0f, acc);
     }
   }
   acc = group_sum<kLanes1>(acc);
