@@ -178,7 +178,8 @@ int lm_cost(const lm_geom *G, const float *x, const int16_t *ev, const float *s,
 typedef struct lm_plan lm_plan;
 
 /* Device bytes a plan for n_ev events and n_sub subsets will allocate,
- * including the temporary memory of lm_plan_create; host output *bytes.
+ * including the temporary memory of lm_plan_create and lm_spdhg_init (which
+ * back projects in batches that fit it); host output *bytes.
  * Used to admit reconstructions against an HBM budget.  lm_plan_bytes
  * counts the base plan; lm_plan_bytes_ex adds the optional parts named in
  * `parts` (an OR of the LM_PART_* flags): the directional TV prior

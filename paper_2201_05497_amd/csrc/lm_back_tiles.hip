@@ -248,35 +248,44 @@ constexpr int kMaxListTiles = 36 << 10;
 constexpr long long kListSegBytes = 1LL << 30;
 
 int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const int4 *rec, long long n, float *img,
-                      hipStream_t st, bool &queued) {
+                      size_t room, hipStream_t st, bool &queued) {
   queued = false;
   if (n < kMinListEvents || !segs_supported(g)) return LM_OK;
   const TileGeom tg = tile_geom(g.n, kTL);
   if (tg.ntiles > kMaxListTiles) return LM_OK;
   const int maxp = lmh::max_planes(g, W_BIN);
   const long long pe = segs_per_event(g, maxp, kTL);
-  const long long batch = std::min(std::min(n, 1LL << 30), kListSegBytes / (4 * pe));
-  if (batch < kMinListEvents) return LM_OK;  // very unequal voxel sides: too many tiles per event to plan for
-  const long long items = batch * pe / kItemMin + tg.ntiles;
   // events of a binning workgroup: enough workgroups to fill the chip, few
   // enough that their histograms (cleared, added and kept per workgroup)
   // stay a small part
-  const int chunk =
-      (int)std::min<long long>(4096, ((batch + 1023) / 1024 + kBinBlock - 1) / kBinBlock * kBinBlock);
-  const long long rows = (batch + chunk - 1) / chunk;
+  auto chunk_of = [](long long batch) {
+    return (int)std::min<long long>(4096, ((batch + 1023) / 1024 + kBinBlock - 1) / kBinBlock * kBinBlock);
+  };
   SegRay *rays = nullptr;
   uint2 *item = nullptr;
   unsigned *seg = nullptr, *tot = nullptr, *off = nullptr, *nitems = nullptr, *base = nullptr;
   float *val = nullptr;
-  lmh::Slab arrays;
-  arrays.add(&rays, batch);
-  arrays.add(&item, items);
-  arrays.add(&seg, batch * pe);
-  arrays.add(&val, batch);
-  arrays.add(&tot, tg.ntiles);
-  arrays.add(&off, tg.ntiles + 1);
-  arrays.add(&nitems, 2);
-  arrays.add(&base, rows * tg.ntiles);
+  auto arrays_of = [&](long long batch) {
+    lmh::Slab a;
+    a.add(&rays, batch);
+    a.add(&item, batch * pe / kItemMin + tg.ntiles);
+    a.add(&seg, batch * pe);
+    a.add(&val, batch);
+    a.add(&tot, tg.ntiles);
+    a.add(&off, tg.ntiles + 1);
+    a.add(&nitems, 2);
+    a.add(&base, (batch + chunk_of(batch) - 1) / chunk_of(batch) * tg.ntiles);
+    return a;
+  };
+  const size_t tof_bytes = g.tof_on ? kTofTabMax * sizeof(float4) : 0;
+  long long batch = std::min(std::min(n, 1LL << 30), kListSegBytes / (4 * pe));
+  if (room != SIZE_MAX) {
+    while (batch >= kMinListEvents && arrays_of(batch).bytes() + tof_bytes > room) batch -= batch / 16;
+    if (batch >= kMinListEvents) batch = (n + (n + batch - 1) / batch - 1) / ((n + batch - 1) / batch);  // equal ones
+  }
+  if (batch < kMinListEvents) return LM_OK;  // no room, or very unequal voxel sides: too many tiles per event
+  const int chunk = chunk_of(batch);
+  lmh::Slab arrays = arrays_of(batch);
   void *tmp = nullptr;
   {
     const hipError_t e = arrays.alloc(st, &tmp);

@@ -120,7 +120,8 @@ int build_tof_table(const GeomDev &g, TofTab &t, float4 **tab, hipStream_t st);
 // Plan-internal event records: int4 {id1, id2, k, s bits}.
 int launch_fwd_rec(const GeomDev &g, const float *x, const int4 *rec, long long n, float *out,
                    hipStream_t st);
-int launch_back_rec(const GeomDev &g, const float *v, const int4 *rec, long long n, float *img,
+// room: the bytes of device temporaries that launch_back_rec may take.
+int launch_back_rec(const GeomDev &g, const float *v, const int4 *rec, long long n, float *img, size_t room,
                     hipStream_t st);
 // Fused data update of one subset (Algorithm 2, data branch); cdual holds
 // the complement 1 - y of the dual variable.
@@ -140,8 +141,14 @@ class Slab {
   template <class T>
   void add(T **p, size_t count) {
     *p = nullptr;
+    bytes_ = (bytes_ + 255) / 256 * 256;
     parts_.push_back({p, bytes_});
-    bytes_ += (std::max<size_t>(count, 1) * sizeof(T) + 255) / 256 * 256;
+    bytes_ += std::max<size_t>(count, 1) * sizeof(T);
+  }
+  // the most bytes that one part takes
+  template <class T>
+  static size_t padded(size_t count) {
+    return (std::max<size_t>(count, 1) * sizeof(T) + 255) / 256 * 256;
   }
   size_t bytes() const { return bytes_; }
   // *base: the allocation, for hipFreeAsync; nullptr when it failed

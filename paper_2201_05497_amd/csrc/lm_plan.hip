@@ -99,6 +99,9 @@ struct lm_plan {
   bool g_internal = false;
   float *g0 = nullptr;
   std::vector<void *> allocs;
+  // bytes that lm_plan_bytes promises beyond what lm_plan_create left
+  // allocated, for the temporaries of lm_spdhg_init
+  size_t room = 0;
   bool initialized = false;
   long long u = 0;
   hipStream_t last = nullptr;
@@ -321,14 +324,14 @@ struct Sizes {
   size_t persistent, temporary;
 };
 
-Sizes plan_sizes(long long n, int nsub, long long nvox, long long ne, int ncomp) {
+Sizes plan_sizes(long long n, int nsub, long long ne, int ncomp) {
+  using lmh::Slab;
   Sizes s;
-  const size_t N = (size_t)n, E = (size_t)ne;
-  s.persistent = N * (sizeof(int4) + 5 * sizeof(float) + sizeof(int)) + (size_t)(nsub + 1) * sizeof(int) +
-                 E * sizeof(float) * (7 + 2 * (size_t)ncomp);
+  s.persistent = Slab::padded<int4>(n) + 5 * Slab::padded<float>(n) + Slab::padded<int>(n) +
+                 Slab::padded<int>(nsub + 1) + 7 * Slab::padded<float>(ne) + 2 * Slab::padded<float>(ne * ncomp);
   const size_t cap = hash_capacity(n);
-  s.temporary = cap * (sizeof(unsigned long long) + sizeof(unsigned)) + N * sizeof(unsigned) +
-                E * sizeof(float) + 64;
+  s.temporary = Slab::padded<unsigned long long>(cap) + Slab::padded<unsigned>(cap) + Slab::padded<unsigned>(n) +
+                Slab::padded<float>(ne) + 64;  // and the flags of the validation and the sensitivity
   return s;
 }
 
@@ -399,7 +402,7 @@ int lm_plan_bytes_ex(const lm_geom *G, int64_t n_ev, int32_t n_sub, int32_t part
              "unknown plan parts 0x%x", (unsigned)parts);
   const int ncomp = G->n[2] > 1 ? 3 : 2;
   const long long E = lmk::layout_size(lmh::brick_layout(G->n));
-  const Sizes s = plan_sizes(n_ev, n_sub, lmh::nvox_of(G->n), E, ncomp);
+  const Sizes s = plan_sizes(n_ev, n_sub, E, ncomp);
   lmk::GeomDev gb = g;
   gb.lay = lmh::brick_layout(G->n);
   size_t extra = lmk::tile_bytes_bound(gb, n_ev, n_sub);
@@ -562,6 +565,11 @@ int lm_plan_create(const lm_geom *G, const int16_t *ev, const float *s, int64_t 
   step(hipStreamSynchronize(st), "plan create");
   free_tmp();
   if (rc != LM_OK) return fail(rc);
+  {
+    const Sizes sizes = plan_sizes(N, n_sub, E, p->ncomp);
+    const size_t tiles = lmk::tile_bytes_bound(p->g, N, n_sub);
+    p->room = sizes.temporary + (tiles > p->tiles.bytes ? tiles - p->tiles.bytes : 0);
+  }
   *out = p;
   return LM_OK;
 }
@@ -578,7 +586,7 @@ int lm_spdhg_init(lm_plan *p, const float *x0, void *stream) {
     if (int rc = lmk::launch_fwd_rec(p->g, p->xint, p->rec, N, p->c, st)) return rc;
     hipLaunchKernelGGL(k_init_dual, dim3(grid_for(N)), dim3(kBlock), 0, st, p->c, p->rec, p->mu, p->tmp, N);
     LM_TRY_HIP(hipGetLastError());
-    if (int rc = lmk::launch_back_rec(p->g, p->tmp, p->rec, N, p->z, st)) return rc;
+    if (int rc = lmk::launch_back_rec(p->g, p->tmp, p->rec, N, p->z, p->room, st)) return rc;
   } else if (N > 0) {
     // P = G B: y from G (B x0); z gains B G^T((y - 1) / mu)
     if (int rc = lmk::launch_blur(p->G.n, p->lay, E, p->blur, p->xint, p->xb, p->bt1, p->bt2, st)) return rc;
@@ -587,7 +595,7 @@ int lm_spdhg_init(lm_plan *p, const float *x0, void *stream) {
     LM_TRY_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_fill, dim3(grid_for(E)), dim3(kBlock), 0, st, p->dz, 0.0f, E);
     LM_TRY_HIP(hipGetLastError());
-    if (int rc = lmk::launch_back_rec(p->g, p->tmp, p->rec, N, p->dz, st)) return rc;
+    if (int rc = lmk::launch_back_rec(p->g, p->tmp, p->rec, N, p->dz, p->room, st)) return rc;
     if (int rc = lmk::launch_blur(p->G.n, p->lay, E, p->blur, p->dz, p->dzb, p->bt1, p->bt2, st)) return rc;
     hipLaunchKernelGGL(k_add, dim3(grid_for(E)), dim3(kBlock), 0, st, p->z, p->dzb, E);
     LM_TRY_HIP(hipGetLastError());

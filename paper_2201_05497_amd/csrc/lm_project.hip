@@ -424,21 +424,22 @@ int launch_fwd(const GeomDev &g, const float *x, const int16_t *ev, long long n,
 // By tile, or per event where the list is short or the tile path does not
 // apply.
 static int back_any(const GeomDev &g, const float *v, const int16_t *ev, const int4 *rec, long long n, float *img,
-                    hipStream_t st) {
+                    size_t room, hipStream_t st) {
   if (n == 0) return LM_OK;
   bool queued = false;
-  if (int rc = launch_back_tiles(g, v, ev, rec, n, img, st, queued)) return rc;
+  if (int rc = launch_back_tiles(g, v, ev, rec, n, img, room, st, queued)) return rc;
   if (queued) return LM_OK;
   return ev ? back_impl(g, v, CallerEvents{ev}, n, img, st) : back_impl(g, v, PlanEvents{rec}, n, img, st);
 }
 int launch_back(const GeomDev &g, const float *v, const int16_t *ev, long long n, float *img, hipStream_t st) {
-  return back_any(g, v, ev, nullptr, n, img, st);
+  return back_any(g, v, ev, nullptr, n, img, SIZE_MAX, st);
 }
 int launch_fwd_rec(const GeomDev &g, const float *x, const int4 *rec, long long n, float *out, hipStream_t st) {
   return fwd_impl(g, x, PlanEvents{rec}, n, out, st);
 }
-int launch_back_rec(const GeomDev &g, const float *v, const int4 *rec, long long n, float *img, hipStream_t st) {
-  return back_any(g, v, nullptr, rec, n, img, st);
+int launch_back_rec(const GeomDev &g, const float *v, const int4 *rec, long long n, float *img, size_t room,
+                    hipStream_t st) {
+  return back_any(g, v, nullptr, rec, n, img, room, st);
 }
 
 int launch_sens(const GeomDev &g, float *img, hipStream_t st) {

@@ -230,10 +230,11 @@ TileGeom tile_geom(const int n[3], int te);
 long long segs_per_event(const GeomDev &g, int maxp, int te);
 
 // Back projection of a caller's list (ev, or a plan's records rec when ev is
-// NULL) by tile, img += P^T v in the layout of g (lm_back_tiles.hip).
-// queued is false, with nothing enqueued, when the list is too short, the
-// image does not qualify or the temporaries do not fit.
+// NULL) by tile, img += P^T v in the layout of g (lm_back_tiles.hip), in
+// batches whose temporaries take at most `room` bytes.  queued is false, with
+// nothing enqueued, when the list is too short, the image does not qualify or
+// the temporaries do not fit.
 int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const int4 *rec, long long n, float *img,
-                      hipStream_t st, bool &queued);
+                      size_t room, hipStream_t st, bool &queued);
 
 }  // namespace lmk

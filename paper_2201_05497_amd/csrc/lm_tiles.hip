@@ -399,12 +399,13 @@ size_t tile_bytes_bound(const GeomDev &g, long long n, int nsub) {
   if (nmax < kMinEventsPerTile * tg.ntiles) return 0;
   const long long per_event = segs_per_event(g, lmh::max_planes(g, W_BIN), kTE);
   const long long nbin = (long long)nsub * tg.ntiles, nblk = (nbin + kScanB - 1) / kScanB;
-  const size_t kept = (size_t)(n * per_event) * sizeof(unsigned) + (size_t)(nbin + 1) * sizeof(long long) +
-                      (size_t)tg.ntiles * sizeof(int) + (size_t)nmax * (sizeof(SegRay) + sizeof(float)) +
-                      (size_t)kTofTabMax * sizeof(float4);
-  const size_t temporary = (size_t)nbin * sizeof(unsigned) + (size_t)tg.ntiles * sizeof(unsigned long long) +
-                           (size_t)nblk * 2 * sizeof(long long) +
-                           2 * (size_t)(nsub + 1) * sizeof(long long) + 8;
+  using lmh::Slab;
+  const size_t kept = Slab::padded<unsigned>(n * per_event) + Slab::padded<long long>(nbin + 1) +
+                      Slab::padded<int>(tg.ntiles) + Slab::padded<SegRay>(nmax) + Slab::padded<float>(nmax) +
+                      Slab::padded<float4>(kTofTabMax);
+  const size_t temporary = Slab::padded<unsigned>(nbin) + Slab::padded<unsigned long long>(tg.ntiles) +
+                           Slab::padded<long long>(nblk) + Slab::padded<long long>(nblk + 1) +
+                           2 * Slab::padded<long long>(nsub + 1);
   return kept + temporary;
 }
 
@@ -533,6 +534,7 @@ int build_tiles(const GeomDev &g, const int4 *rec, const std::vector<int> &off, 
   tp.maxp = maxp;
   tp.rays = rays;
   tp.cf = cf;
+  tp.bytes = (size_t)(nbin + 1) * sizeof(long long) + lists.bytes() + (tab ? tof_tab_size(tt) * sizeof(float4) : 0);
   return LM_OK;
 }
 

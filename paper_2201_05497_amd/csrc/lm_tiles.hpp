@@ -26,6 +26,7 @@ struct TilePlan {
   float *cf = nullptr;
   TofTab tt{};                   // layout of the tabulated TOF weights
   float4 *tab = nullptr;         // the table (nullptr: erfc, or no TOF)
+  size_t bytes = 0;              // device bytes of the above
 };
 
 bool tiles_supported(const GeomDev &g);
