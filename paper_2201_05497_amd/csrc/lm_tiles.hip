@@ -54,9 +54,12 @@ constexpr int kBlock1 = 256;
 constexpr long long kMinEventsPerTile = 4;
 constexpr int kBinBlock = 512;         // threads of the binning kernels
 constexpr int kBinChunk = 4096;        // events of a binning workgroup
-// Tiles of an image: the histogram of a binning workgroup, 4 bytes per tile,
-// is in LDS.
-constexpr int kMaxTiles = 36 << 10;
+// Tiles that a binning workgroup counts: its histogram, 4 bytes per tile, is
+// in LDS.  Images of more tiles are binned in ranges of tiles, by a workgroup
+// each, which walk the same events: a plan of 400x400x128 (40000 tiles, two
+// ranges) and 1.6e6 events in 8 subsets takes 7 ms to create and 214 us per
+// data update, per event 3 ms and 410 us.
+constexpr int kHistTiles = 36 << 10;
 
 // Planes an event may visit: the segment lists' bound per event grows with
 // them, to 1 KB on a grid of 200 planes without TOF, more than the per-event
@@ -74,6 +77,12 @@ __device__ __forceinline__ void bin_range(const long long *sub, long long &a, lo
   b = min(sub[blockIdx.y + 1], a + kBinChunk);
 }
 
+// The tiles of binning workgroup (blockIdx.z): t0 and the number of them.
+__device__ __forceinline__ int tile_range(const TileGeom &tg, int &t0) {
+  t0 = blockIdx.z * kHistTiles;
+  return min(tg.ntiles - t0, kHistTiles);
+}
+
 // cnt[subset ntiles + tile] = the segments of the subset in the tile.  One
 // LDS histogram per workgroup and one global atomic per workgroup and tile.
 __global__ __launch_bounds__(kBinBlock) void k_tile_count(GeomDev g, TileGeom tg, int maxp,
@@ -83,16 +92,20 @@ __global__ __launch_bounds__(kBinBlock) void k_tile_count(GeomDev g, TileGeom tg
   long long a, b;
   bin_range(sub, a, b);
   if (a >= b) return;
-  for (int t = threadIdx.x; t < tg.ntiles; t += kBinBlock) h[t] = 0u;
+  int t0;
+  const int nt = tile_range(tg, t0);
+  for (int t = threadIdx.x; t < nt; t += kBinBlock) h[t] = 0u;
   __syncthreads();
   for (long long e = a + threadIdx.x; e < b; e += kBinBlock) {
     const int4 rc = rec[e];
     const SegRay s = pack_seg_ray(setup_ray(g, rc.x, rc.y, rc.z, W_BIN, maxp));
-    for_each_segment<kTE>(g, s, tg, [&](int t) { atomicAdd(&h[t], 1u); });
+    for_each_segment<kTE>(g, s, tg, [&](int t) {
+      if ((unsigned)(t - t0) < (unsigned)nt) atomicAdd(&h[t - t0], 1u);
+    });
   }
   __syncthreads();
-  unsigned *c = cnt + (long long)blockIdx.y * tg.ntiles;
-  for (int t = threadIdx.x; t < tg.ntiles; t += kBinBlock)
+  unsigned *c = cnt + (long long)blockIdx.y * tg.ntiles + t0;
+  for (int t = threadIdx.x; t < nt; t += kBinBlock)
     if (h[t]) atomicAdd(c + t, h[t]);
 }
 
@@ -109,7 +122,9 @@ __global__ __launch_bounds__(kBinBlock) void k_tile_place(GeomDev g, TileGeom tg
   long long a, b;
   bin_range(sub, a, b);
   if (a >= b) return;
-  for (int t = threadIdx.x; t < tg.ntiles; t += kBinBlock) h[t] = 0u;
+  int t0;
+  const int nt = tile_range(tg, t0);
+  for (int t = threadIdx.x; t < nt; t += kBinBlock) h[t] = 0u;
   __syncthreads();
   const long long first = off[(long long)blockIdx.y * tg.ntiles], s0 = sub[blockIdx.y];
   unsigned *sg = seg + first;  // a subset's segments: below 2^32
@@ -117,16 +132,17 @@ __global__ __launch_bounds__(kBinBlock) void k_tile_place(GeomDev g, TileGeom tg
     for (long long e = a + threadIdx.x; e < b; e += kBinBlock) {
       const int4 rc = rec[e];
       const SegRay s = pack_seg_ray(setup_ray(g, rc.x, rc.y, rc.z, W_BIN, maxp));
-      if (pass == 0)
-        for_each_segment<kTE>(g, s, tg, [&](int t) { atomicAdd(&h[t], 1u); });
-      else
-        for_each_segment<kTE>(g, s, tg, [&](int t) { sg[atomicAdd(&h[t], 1u)] = (unsigned)(e - s0); });
+      for_each_segment<kTE>(g, s, tg, [&](int t) {
+        if ((unsigned)(t - t0) >= (unsigned)nt) return;
+        const unsigned at = atomicAdd(&h[t - t0], 1u);
+        if (pass == 1) sg[at] = (unsigned)(e - s0);
+      });
     }
     __syncthreads();
     if (pass == 0) {
-      const long long *o = off + (long long)blockIdx.y * tg.ntiles;
-      unsigned *f = fill + (long long)blockIdx.y * tg.ntiles;
-      for (int t = threadIdx.x; t < tg.ntiles; t += kBinBlock)
+      const long long *o = off + (long long)blockIdx.y * tg.ntiles + t0;
+      unsigned *f = fill + (long long)blockIdx.y * tg.ntiles + t0;
+      for (int t = threadIdx.x; t < nt; t += kBinBlock)
         if (h[t]) h[t] = (unsigned)(o[t] - first) + atomicAdd(f + t, h[t]);
       __syncthreads();
     }
@@ -386,10 +402,10 @@ inline unsigned blocks(long long n, int per) { return (unsigned)((n + per - 1) /
 
 namespace lmk {
 
-// 3D plans (4x4x4 bricks) whose tiles fit the binning histogram.
+// 3D plans (4x4x4 bricks) whose rays fit the record and the planned lists.
 bool tiles_supported(const GeomDev &g) {
   if (g.n[2] < 2 || g.lay.sx != 2 || g.lay.sy != 2 || g.lay.sz != 2) return false;
-  return segs_supported(g) && tile_geom(g.n, kTE).ntiles <= kMaxTiles && lmh::max_planes(g, W_BIN) <= kMaxTilePlanes;
+  return segs_supported(g) && lmh::max_planes(g, W_BIN) <= kMaxTilePlanes;
 }
 
 size_t tile_bytes_bound(const GeomDev &g, long long n, int nsub) {
@@ -466,12 +482,13 @@ int build_tiles(const GeomDev &g, const int4 *rec, const std::vector<int> &off, 
           hipSuccess ||
       (e = hipMemsetAsync(cnt, 0, nbin * sizeof(unsigned), st)) != hipSuccess)
     return fail(e);
-  const size_t lds = (size_t)tg.ntiles * sizeof(unsigned);
+  const size_t lds = (size_t)std::min(tg.ntiles, kHistTiles) * sizeof(unsigned);
+  const unsigned ranges = blocks(tg.ntiles, kHistTiles);
   // subsets in groups of at most 2^15 (the grid's y extent)
   constexpr int kGroup = 1 << 15;
   const unsigned bx = blocks(nlargest, kBinChunk);
   for (int i = 0; i < nsub; i += kGroup)
-    hipLaunchKernelGGL(k_tile_count, dim3(bx, std::min(kGroup, nsub - i)), dim3(kBinBlock), lds, st, g, tg, maxp, rec,
+    hipLaunchKernelGGL(k_tile_count, dim3(bx, std::min(kGroup, nsub - i), ranges), dim3(kBinBlock), lds, st, g, tg, maxp, rec,
                        sub + i, cnt + (long long)i * tg.ntiles);
   hipLaunchKernelGGL(k_tile_load, dim3(blocks(tg.ntiles, 256)), dim3(256), 0, st, cnt, tg.ntiles, nsub, load);
   hipLaunchKernelGGL(k_block_sums, dim3((unsigned)nblk), dim3(kScanB), 0, st, cnt, nbin, bsum);
@@ -512,7 +529,7 @@ int build_tiles(const GeomDev &g, const int4 *rec, const std::vector<int> &off, 
       (e = hipMemsetAsync(cnt, 0, nbin * sizeof(unsigned), st)) != hipSuccess)
     return fail(e);
   for (int i = 0; i < nsub; i += kGroup)
-    hipLaunchKernelGGL(k_tile_place, dim3(bx, std::min(kGroup, nsub - i)), dim3(kBinBlock), lds, st, g, tg, maxp, rec,
+    hipLaunchKernelGGL(k_tile_place, dim3(bx, std::min(kGroup, nsub - i), ranges), dim3(kBinBlock), lds, st, g, tg, maxp, rec,
                        sub + i, soff + (long long)i * tg.ntiles, cnt + (long long)i * tg.ntiles, seg);
   if ((e = hipGetLastError()) != hipSuccess) return fail(e);
   // the host order vector dies with this call

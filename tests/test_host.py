@@ -154,6 +154,22 @@ def test_plan_bytes_grow_with_events_and_image():
     assert t - plan_bytes(20000, (16, 16, 8), n_sub=400) > 20000 * 4
 
 
+def test_plan_bytes_count_tile_lists_of_large_images():
+    """An image of 50000 8x8x8 tiles has tile lists from 4 events per tile of
+    the largest subset on, as smaller ones have."""
+    import ctypes
+    from paper_2201_05497_amd import _lib as L
+    if not os.path.exists(L.LIB_PATH):
+        pytest.skip("library not built")
+    lib = L.load()
+    g = L.LMGeom(0x1000, 8, 1, (ctypes.c_int32 * 3)(400, 400, 160), (ctypes.c_double * 3)(2.0, 2.0, 2.0),
+                 5, 10.0, 20.0, 3.0, 1)
+    b = [ctypes.c_size_t(0), ctypes.c_size_t(0)]
+    for k in range(2):
+        assert lib.lm_plan_bytes(ctypes.byref(g), 200000 - 1 + k, 1, ctypes.byref(b[k])) == 0
+    assert b[1].value - b[0].value > 200000 * 4
+
+
 def test_sort_by_dominant_axis():
     """The large workload's input order: grouped by dominant axis (x, then
     y, then z), chronological inside each group, the same events and s."""
