@@ -137,12 +137,13 @@ __device__ __forceinline__ TileLane<TE> tile_lane(int ox, int oy, int oz, int p)
 }
 
 // Adds the sample of ray s on the lane's plane, with event value val, where
-// `on`.  A value that is not finite reaches the corners of the samples of TOF
-// weight above 0 (also corners of weight 0).  The corner's place in the
+// `on`.  With ANY the value may be one that is not finite, which reaches the
+// corners of the samples of TOF weight above 0 (also corners of weight 0); else
+// it is finite.  The corner's place in the
 // accumulators is computed in float (whole numbers below 2^24, exact): the
 // voxel coordinates are floats already and an integer product takes four
 // times as long.
-template <int TM, int TE>
+template <int TM, int TE, bool ANY>
 __device__ __forceinline__ void add_sample(const GeomDev &g, const TileLane<TE> &t, const SegRay &s, float val,
                                            bool on, float D, const TofTab &tu, const float4 *tab, char *acc) {
   using S = AccShape<TE>;
@@ -168,7 +169,7 @@ __device__ __forceinline__ void add_sample(const GeomDev &g, const TileLane<TE> 
         const float vh = fmaf(0.5f, D, tc);
         w = tof_weight(vh, vh - D, g.vclip, g.inv_norm);
       }
-      v = w != 0.0f ? val * w : 0.0f;
+      v = ANY && w == 0.0f ? 0.0f : val * w;
     }
     const float d1 = x_dom ? 8.0f * S::Y : 8.0f, d2 = z_dom ? 8.0f * S::Y : 8.0f * S::Z;
     const int at = (int)fmaf(l1, d1, fmaf(l2, d2, sel3(a, t.ax, t.ay, t.az)));
@@ -189,7 +190,7 @@ __device__ __forceinline__ void add_sample(const GeomDev &g, const TileLane<TE> 
 // ray one step before they are used, in that order, so that waiting for a
 // number leaves the rays in flight; two steps per turn of the loop, so that
 // no register is copied (a copy would wait for the loads).  cnt < 2^28.
-template <int TM, int TE>
+template <int TM, int TE, bool ANY>
 __device__ __forceinline__ void add_segments(const GeomDev &g, const TileLane<TE> &t, const unsigned *__restrict__ seg,
                                              int cnt, const SegRay *__restrict__ rays,
                                              const float *__restrict__ val, float D, const TofTab &tu,
@@ -215,11 +216,11 @@ __device__ __forceinline__ void add_segments(const GeomDev &g, const TileLane<TE
     eA = num(byte + 2 * bstep);
     const SegRay rB = ray(eB);
     const float vB = val[eB];
-    add_sample<TM, TE>(g, t, rA, vA, byte <= lim, D, tu, tab, (char *)acc);
+    add_sample<TM, TE, ANY>(g, t, rA, vA, byte <= lim, D, tu, tab, (char *)acc);
     eB = num(byte + 3 * bstep);
     rA = ray(eA);
     vA = val[eA];
-    add_sample<TM, TE>(g, t, rB, vB, byte + bstep <= lim, D, tu, tab, (char *)acc);
+    add_sample<TM, TE, ANY>(g, t, rB, vB, byte + bstep <= lim, D, tu, tab, (char *)acc);
   }
 }
 
