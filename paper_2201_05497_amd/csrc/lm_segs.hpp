@@ -189,7 +189,9 @@ __device__ __forceinline__ void add_sample(const GeomDev &g, const TileLane<TE> 
 // them and every nw-th after.  A segment's number is loaded two steps and its
 // ray one step before they are used, in that order, so that waiting for a
 // number leaves the rays in flight; two steps per turn of the loop, so that
-// no register is copied (a copy would wait for the loads).  cnt < 2^28.
+// no register is copied (a copy would wait for the loads).  cnt is at most
+// kMaxSegments, whose byte offsets and those of the loads ahead fit 32 bits.
+constexpr int kMaxSegments = 1 << 29;
 template <int TM, int TE, bool ANY>
 __device__ __forceinline__ void add_segments(const GeomDev &g, const TileLane<TE> &t, const unsigned *__restrict__ seg,
                                              int cnt, const SegRay *__restrict__ rays,

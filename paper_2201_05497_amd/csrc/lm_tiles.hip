@@ -515,6 +515,10 @@ int build_tiles(const GeomDev &g, const int4 *rec, const std::vector<int> &off, 
   std::vector<int> order(tg.ntiles);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return hload[a] > hload[b]; });
+  if (hload[order[0]] > (unsigned long long)kMaxSegments) {
+    drop(false);
+    return LM_OK;  // so many events on an image of a few tiles
+  }
   lmh::Slab lists;
   lists.add(&seg, total);
   lists.add(&ord, tg.ntiles);
