@@ -221,19 +221,20 @@ bool segs_supported(const GeomDev &g) {
 }
 
 long long segs_per_event(const GeomDev &g, int maxp, int te) {
-  // tiles a chunk of te planes along axis a can reach along axis b: the
-  // corners span at most (te - 1) h_a / h_b + 3 voxels (and at most the axis)
-  long long per_chunk = 1;
+  // chunks of te planes along axis a, and tiles a chunk can reach along axis
+  // b: the corners span at most (te - 1) h_a / h_b + 3 voxels (and at most the
+  // axis)
+  long long most = 1;
   for (int a = 0; a < 3; ++a) {
-    long long m = 1;
+    long long m = (std::min(maxp, g.n[a]) + te - 2) / te + 1;
     for (int b = 0; b < 3; ++b) {
       if (b == a) continue;
       const long long span = (long long)std::floor((te - 1) * g.h[a] / g.h[b]) + 3;
       m *= std::min<long long>((span + te - 2) / te + 1, (g.n[b] + te - 1) / te);
     }
-    per_chunk = std::max(per_chunk, m);
+    most = std::max(most, m);
   }
-  return ((maxp + te - 2) / te + 1) * per_chunk;
+  return most;
 }
 
 // Lists of at least this many events go by tile: the binning and the clearing
@@ -247,48 +248,76 @@ constexpr int kMaxListTiles = 36 << 10;
 // Bytes of the segment numbers of a batch; longer lists go in batches.
 constexpr long long kListSegBytes = 1LL << 30;
 
+// Events of a binning workgroup: enough workgroups to fill the chip, few
+// enough that their histograms (cleared, added and kept per workgroup) stay a
+// small part.
+static int bin_chunk(long long batch) {
+  return (int)std::min<long long>(4096, ((batch + 1023) / 1024 + kBinBlock - 1) / kBinBlock * kBinBlock);
+}
+
+namespace {
+// The temporaries of a batch.
+struct BackArrays {
+  SegRay *rays;
+  uint2 *item;
+  unsigned *seg, *tot, *off, *nitems, *base;
+  float *val;
+  lmh::Slab slab;
+  BackArrays(long long batch, long long pe, int ntiles) {
+    const int chunk = bin_chunk(batch);
+    slab.add(&rays, batch);
+    slab.add(&item, batch * pe / kItemMin + ntiles);
+    slab.add(&seg, batch * pe);
+    slab.add(&val, batch);
+    slab.add(&tot, ntiles);
+    slab.add(&off, ntiles + 1);
+    slab.add(&nitems, 2);
+    slab.add(&base, (batch + chunk - 1) / chunk * ntiles);
+  }
+  BackArrays(const BackArrays &) = delete;  // the slab holds the addresses of the others
+  BackArrays &operator=(const BackArrays &) = delete;
+};
+
+// A list's way by tile; batch 0: per event.
+struct BackShape {
+  TileGeom tg;
+  int maxp;
+  long long pe, batch;
+  BackShape(const GeomDev &g, long long n) : tg(tile_geom(g.n, kTL)), maxp(lmh::max_planes(g, W_BIN)) {
+    pe = segs_per_event(g, maxp, kTL);
+    batch = std::min(std::min(n, 1LL << 30), kListSegBytes / (4 * pe));
+    // very unequal voxel sides: too many tiles per event to plan for
+    if (batch < kMinListEvents || tg.ntiles > kMaxListTiles || !segs_supported(g)) batch = 0;
+  }
+  size_t bytes(const GeomDev &g, long long events) const {
+    return BackArrays(events, pe, tg.ntiles).slab.bytes() + (g.tof_on ? kTofTabMax * sizeof(float4) : 0);
+  }
+};
+}  // namespace
+
+size_t back_tiles_min_bytes(const GeomDev &g, long long n) {
+  const BackShape s(g, n);
+  return s.batch ? s.bytes(g, kMinListEvents) : 0;
+}
+
 int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const int4 *rec, long long n, float *img,
                       size_t room, hipStream_t st, bool &queued) {
   queued = false;
-  if (n < kMinListEvents || !segs_supported(g)) return LM_OK;
-  const TileGeom tg = tile_geom(g.n, kTL);
-  if (tg.ntiles > kMaxListTiles) return LM_OK;
-  const int maxp = lmh::max_planes(g, W_BIN);
-  const long long pe = segs_per_event(g, maxp, kTL);
-  // events of a binning workgroup: enough workgroups to fill the chip, few
-  // enough that their histograms (cleared, added and kept per workgroup)
-  // stay a small part
-  auto chunk_of = [](long long batch) {
-    return (int)std::min<long long>(4096, ((batch + 1023) / 1024 + kBinBlock - 1) / kBinBlock * kBinBlock);
-  };
-  SegRay *rays = nullptr;
-  uint2 *item = nullptr;
-  unsigned *seg = nullptr, *tot = nullptr, *off = nullptr, *nitems = nullptr, *base = nullptr;
-  float *val = nullptr;
-  auto arrays_of = [&](long long batch) {
-    lmh::Slab a;
-    a.add(&rays, batch);
-    a.add(&item, batch * pe / kItemMin + tg.ntiles);
-    a.add(&seg, batch * pe);
-    a.add(&val, batch);
-    a.add(&tot, tg.ntiles);
-    a.add(&off, tg.ntiles + 1);
-    a.add(&nitems, 2);
-    a.add(&base, (batch + chunk_of(batch) - 1) / chunk_of(batch) * tg.ntiles);
-    return a;
-  };
-  const size_t tof_bytes = g.tof_on ? kTofTabMax * sizeof(float4) : 0;
-  long long batch = std::min(std::min(n, 1LL << 30), kListSegBytes / (4 * pe));
-  if (room != SIZE_MAX) {
-    while (batch >= kMinListEvents && arrays_of(batch).bytes() + tof_bytes > room) batch -= batch / 16;
-    if (batch >= kMinListEvents) batch = (n + (n + batch - 1) / batch - 1) / ((n + batch - 1) / batch);  // equal ones
+  const BackShape shape(g, n);
+  long long batch = shape.batch;
+  if (room != SIZE_MAX && batch) {
+    while (batch > kMinListEvents && shape.bytes(g, batch) > room)
+      batch = std::max(kMinListEvents, batch - batch / 16);
+    if (shape.bytes(g, batch) > room) batch = 0;
+    else batch = (n + (n + batch - 1) / batch - 1) / ((n + batch - 1) / batch);  // equal ones
   }
-  if (batch < kMinListEvents) return LM_OK;  // no room, or very unequal voxel sides: too many tiles per event
-  const int chunk = chunk_of(batch);
-  lmh::Slab arrays = arrays_of(batch);
+  if (!batch) return LM_OK;
+  const TileGeom tg = shape.tg;
+  const int maxp = shape.maxp, chunk = bin_chunk(batch);
+  BackArrays a(batch, shape.pe, tg.ntiles);
   void *tmp = nullptr;
   {
-    const hipError_t e = arrays.alloc(st, &tmp);
+    const hipError_t e = a.slab.alloc(st, &tmp);
     if (e == hipErrorOutOfMemory) {
       (void)hipGetLastError();
       return LM_OK;  // the per-event path needs no temporaries
@@ -305,15 +334,16 @@ int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const
     const unsigned nb = (unsigned)((m + chunk - 1) / chunk);
     const int16_t *evo = ev ? ev + 5 * o : nullptr;
     const int4 *reco = ev ? nullptr : rec + o;
-    hipLaunchKernelGGL(k_zero_u32, dim3(std::min(64, (tg.ntiles + 255) / 256)), dim3(256), 0, st, tot,
+    hipLaunchKernelGGL(k_zero_u32, dim3(std::min(64, (tg.ntiles + 255) / 256)), dim3(256), 0, st, a.tot,
                        (long long)tg.ntiles);
     hipLaunchKernelGGL(k_list_count, dim3(nb), dim3(kBinBlock), lds, st, g, tg, maxp, evo, reco, v + o, m, chunk,
-                       rays, val, tot, base, img);
-    hipLaunchKernelGGL(k_list_items, dim3(1), dim3(1024), 0, st, tot, tg.ntiles, off, item, nitems);
-    hipLaunchKernelGGL(k_list_place, dim3(nb), dim3(kBinBlock), lds, st, g, tg, rays, m, chunk, off, base, seg);
-#define LM_LB(TM_)                                                                                                  \
-  hipLaunchKernelGGL((k_list_back<TM_>), dim3(kBackGrid), dim3(kBackBlock), tlds, st, g, tg, off, item, nitems, seg, \
-                     rays, val, tt, tab, img)
+                       a.rays, a.val, a.tot, a.base, img);
+    hipLaunchKernelGGL(k_list_items, dim3(1), dim3(1024), 0, st, a.tot, tg.ntiles, a.off, a.item, a.nitems);
+    hipLaunchKernelGGL(k_list_place, dim3(nb), dim3(kBinBlock), lds, st, g, tg, a.rays, m, chunk, a.off, a.base,
+                       a.seg);
+#define LM_LB(TM_)                                                                                                \
+  hipLaunchKernelGGL((k_list_back<TM_>), dim3(kBackGrid), dim3(kBackBlock), tlds, st, g, tg, a.off, a.item,       \
+                     a.nitems, a.seg, a.rays, a.val, tt, tab, img)
     if (!g.tof_on) LM_LB(kTofNone);
     else if (tab) LM_LB(kTofTable);
     else LM_LB(kTofErfc);

@@ -100,7 +100,7 @@ struct lm_plan {
   float *g0 = nullptr;
   std::vector<void *> allocs;
   // bytes that lm_plan_bytes promises beyond what lm_plan_create left
-  // allocated, for the temporaries of lm_spdhg_init
+  // allocated, for the back projection of lm_spdhg_init
   size_t room = 0;
   bool initialized = false;
   long long u = 0;
@@ -320,18 +320,23 @@ double exact_knorm(const int n[3]) {
   return std::sqrt(s);
 }
 
+// Device bytes of a plan (its geometry in the brick layout): the arrays that
+// it keeps beside its tile lists, and the most that these and the temporaries
+// of its creation and initialisation take.
 struct Sizes {
-  size_t persistent, temporary;
+  size_t persistent, beyond;
 };
 
-Sizes plan_sizes(long long n, int nsub, long long ne, int ncomp) {
+Sizes plan_sizes(const lmk::GeomDev &g, long long n, int nsub, long long ne, int ncomp) {
   using lmh::Slab;
   Sizes s;
   s.persistent = Slab::padded<int4>(n) + 5 * Slab::padded<float>(n) + Slab::padded<int>(n) +
                  Slab::padded<int>(nsub + 1) + 7 * Slab::padded<float>(ne) + 2 * Slab::padded<float>(ne * ncomp);
   const size_t cap = hash_capacity(n);
-  s.temporary = Slab::padded<unsigned long long>(cap) + Slab::padded<unsigned>(cap) + Slab::padded<unsigned>(n) +
-                Slab::padded<float>(ne) + 64;  // and the flags of the validation and the sensitivity
+  const size_t creation = Slab::padded<unsigned long long>(cap) + Slab::padded<unsigned>(cap) +
+                          Slab::padded<unsigned>(n) + Slab::padded<float>(ne) +
+                          64;  // the flags of the validation and the sensitivity
+  s.beyond = lmk::tile_bytes_bound(g, n, nsub) + std::max(creation, lmk::back_tiles_min_bytes(g, n));
   return s;
 }
 
@@ -402,16 +407,15 @@ int lm_plan_bytes_ex(const lm_geom *G, int64_t n_ev, int32_t n_sub, int32_t part
              "unknown plan parts 0x%x", (unsigned)parts);
   const int ncomp = G->n[2] > 1 ? 3 : 2;
   const long long E = lmk::layout_size(lmh::brick_layout(G->n));
-  const Sizes s = plan_sizes(n_ev, n_sub, E, ncomp);
-  lmk::GeomDev gb = g;
-  gb.lay = lmh::brick_layout(G->n);
-  size_t extra = lmk::tile_bytes_bound(gb, n_ev, n_sub);
+  g.lay = lmh::brick_layout(G->n);
+  const Sizes s = plan_sizes(g, n_ev, n_sub, E, ncomp);
+  size_t extra = 0;
   // allocations of the optional parts (each with the one-element minimum of
   // the plan's allocator)
   if (parts & LM_PART_DTV) extra += 2 * (size_t)E * ncomp * sizeof(float);
   if (parts & LM_PART_FACTORS) extra += (size_t)std::max<int64_t>(n_ev, 1) * sizeof(float);
   if (parts & LM_PART_RESOLUTION) extra += 5 * (size_t)E * sizeof(float);  // B x, B dz, 2 temporaries, g0
-  *bytes = s.persistent + s.temporary + extra;
+  *bytes = s.persistent + s.beyond + extra;
   return LM_OK;
 }
 
@@ -566,9 +570,8 @@ int lm_plan_create(const lm_geom *G, const int16_t *ev, const float *s, int64_t 
   free_tmp();
   if (rc != LM_OK) return fail(rc);
   {
-    const Sizes sizes = plan_sizes(N, n_sub, E, p->ncomp);
-    const size_t tiles = lmk::tile_bytes_bound(p->g, N, n_sub);
-    p->room = sizes.temporary + (tiles > p->tiles.bytes ? tiles - p->tiles.bytes : 0);
+    const size_t beyond = plan_sizes(p->g, N, n_sub, E, p->ncomp).beyond;
+    p->room = beyond > p->tiles.bytes ? beyond - p->tiles.bytes : 0;
   }
   *out = p;
   return LM_OK;

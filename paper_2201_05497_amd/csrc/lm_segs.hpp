@@ -237,6 +237,8 @@ long long segs_per_event(const GeomDev &g, int maxp, int te);
 // batches whose temporaries take at most `room` bytes.  queued is false, with
 // nothing enqueued, when the list is too short, the image does not qualify or
 // the temporaries do not fit.
+// room of back_tiles_min_bytes is enough.
+size_t back_tiles_min_bytes(const GeomDev &g, long long n);
 int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const int4 *rec, long long n, float *img,
                       size_t room, hipStream_t st, bool &queued);
 
