@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kBackBlock) void k_list_back(GeomDev g, TileGeom tg
               oz = tile / (tg.ntx * tg.nty) * kTL;
     for (int i = threadIdx.x; i < S::size; i += kBackBlock) acc[i] = 0.0;
     __syncthreads();
-    add_segments<TM, kTL, false>(g, tile_lane<kTL>(ox, oy, oz, lane % kTL), seg + w.y, cnt, rays, val, D, tu, stab, acc,
+    add_segments<TM, kTL>(g, tile_lane<kTL>(ox, oy, oz, lane % kTL), seg + w.y, cnt, rays, val, D, tu, stab, acc,
                           threadIdx.x >> 6, kBackBlock / 64, lane);
     __syncthreads();
     // voxels in brick order: 16 consecutive threads on one 64-byte sector

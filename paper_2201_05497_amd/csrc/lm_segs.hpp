@@ -137,13 +137,12 @@ __device__ __forceinline__ TileLane<TE> tile_lane(int ox, int oy, int oz, int p)
 }
 
 // Adds the sample of ray s on the lane's plane, with event value val, where
-// `on`.  With ANY the value may be one that is not finite, which reaches the
-// corners of the samples of TOF weight above 0 (also corners of weight 0); else
-// it is finite.  The corner's place in the
+// `on`.  A value that is not finite reaches the corners of the samples inside
+// the TOF window (also corners of weight 0).  The corner's place in the
 // accumulators is computed in float (whole numbers below 2^24, exact): the
 // voxel coordinates are floats already and an integer product takes four
 // times as long.
-template <int TM, int TE, bool ANY>
+template <int TM, int TE>
 __device__ __forceinline__ void add_sample(const GeomDev &g, const TileLane<TE> &t, const SegRay &s, float val,
                                            bool on, float D, const TofTab &tu, const float4 *tab, char *acc) {
   using S = AccShape<TE>;
@@ -157,19 +156,15 @@ __device__ __forceinline__ void add_sample(const GeomDev &g, const TileLane<TE> 
   // corner 0 relative to the tile
   const float l1 = (float)(seg_i1(s) - sel3(a, t.oy, t.ox, t.ox)) + fl1;
   const float l2 = (float)(seg_i2(s) - sel3(a, t.oz, t.oz, t.oy)) + fl2;
-  // on the ray, and a corner in the tile
-  if (on && (unsigned)j < (unsigned)seg_np(s) && l1 >= -1.0f && l1 < (float)TE && l2 >= -1.0f && l2 < (float)TE) {
+  const float tc = TM != kTofNone ? fmaf(-fj, s.b.w, s.b.z) : 0.0f;
+  // on the ray, in the window, and a corner in the tile
+  if (on && (unsigned)j < (unsigned)seg_np(s) && (TM != kTofTable || fabsf(tc) < tu.te) && l1 >= -1.0f &&
+      l1 < (float)TE && l2 >= -1.0f && l2 < (float)TE) {
     float v = val;
-    if constexpr (TM != kTofNone) {
-      const float tc = fmaf(-fj, s.b.w, s.b.z);
-      float w;
-      if constexpr (TM == kTofTable) {
-        w = tof_weight_tab(tu, tab, tc);
-      } else {
-        const float vh = fmaf(0.5f, D, tc);
-        w = tof_weight(vh, vh - D, g.vclip, g.inv_norm);
-      }
-      v = ANY && w == 0.0f ? 0.0f : val * w;
+    if constexpr (TM == kTofTable) v *= tof_weight_tab(tu, tab, tc);
+    if constexpr (TM == kTofErfc) {
+      const float vh = fmaf(0.5f, D, tc), w = tof_weight(vh, vh - D, g.vclip, g.inv_norm);
+      v = w != 0.0f ? val * w : 0.0f;
     }
     const float d1 = x_dom ? 8.0f * S::Y : 8.0f, d2 = z_dom ? 8.0f * S::Y : 8.0f * S::Z;
     const int at = (int)fmaf(l1, d1, fmaf(l2, d2, sel3(a, t.ax, t.ay, t.az)));
@@ -192,7 +187,7 @@ __device__ __forceinline__ void add_sample(const GeomDev &g, const TileLane<TE> 
 // no register is copied (a copy would wait for the loads).  cnt is at most
 // kMaxSegments, whose byte offsets and those of the loads ahead fit 32 bits.
 constexpr int kMaxSegments = 1 << 29;
-template <int TM, int TE, bool ANY>
+template <int TM, int TE>
 __device__ __forceinline__ void add_segments(const GeomDev &g, const TileLane<TE> &t, const unsigned *__restrict__ seg,
                                              int cnt, const SegRay *__restrict__ rays,
                                              const float *__restrict__ val, float D, const TofTab &tu,
@@ -218,11 +213,11 @@ __device__ __forceinline__ void add_segments(const GeomDev &g, const TileLane<TE
     eA = num(byte + 2 * bstep);
     const SegRay rB = ray(eB);
     const float vB = val[eB];
-    add_sample<TM, TE, ANY>(g, t, rA, vA, byte <= lim, D, tu, tab, (char *)acc);
+    add_sample<TM, TE>(g, t, rA, vA, byte <= lim, D, tu, tab, (char *)acc);
     eB = num(byte + 3 * bstep);
     rA = ray(eA);
     vA = val[eA];
-    add_sample<TM, TE, ANY>(g, t, rB, vB, byte + bstep <= lim, D, tu, tab, (char *)acc);
+    add_sample<TM, TE>(g, t, rB, vB, byte + bstep <= lim, D, tu, tab, (char *)acc);
   }
 }
 

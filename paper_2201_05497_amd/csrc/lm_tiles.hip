@@ -368,7 +368,7 @@ __global__ __launch_bounds__(NT) void k_tile_back(GeomDev g, TileGeom tg, const 
     for (int i = threadIdx.x; i < tof_tab_size(tt); i += NT) stab[i] = tab[i];
   __syncthreads();
   const int lane = threadIdx.x & 63;
-  add_segments<TM, kTE, true>(g, tile_lane<kTE>(tx * kTE, ty * kTE, tz * kTE, lane % kTE), seg + s0, cnt, rays, cf,
+  add_segments<TM, kTE>(g, tile_lane<kTE>(tx * kTE, ty * kTE, tz * kTE, lane % kTE), seg + s0, cnt, rays, cf,
                         tof_bin_width(g), tof_tab_uniform(tt), stab, acc, threadIdx.x >> 6, NT / 64, lane);
   __syncthreads();
   if (!mine_vox) return;
