@@ -222,14 +222,14 @@ bool segs_supported(const GeomDev &g) {
 
 long long segs_per_event(const GeomDev &g, int maxp, int te) {
   // chunks of te planes along axis a, and tiles a chunk can reach along axis
-  // b: the corners span at most (te - 1) h_a / h_b + 3 voxels (and at most the
-  // axis)
+  // b: the corners span at most (te - 1) h_a / h_b + 3 voxels, one more where
+  // float32 coordinates round across a voxel's edge (and at most the axis)
   long long most = 1;
   for (int a = 0; a < 3; ++a) {
     long long m = (std::min(maxp, g.n[a]) + te - 2) / te + 1;
     for (int b = 0; b < 3; ++b) {
       if (b == a) continue;
-      const long long span = (long long)std::floor((te - 1) * g.h[a] / g.h[b]) + 3;
+      const long long span = (long long)std::floor((te - 1) * g.h[a] / g.h[b]) + 4;
       m *= std::min<long long>((span + te - 2) / te + 1, (g.n[b] + te - 1) / te);
     }
     most = std::max(most, m);
