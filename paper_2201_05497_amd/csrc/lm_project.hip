@@ -527,16 +527,24 @@ int noalloc_scratch(hipStream_t st, float **out) {
 
 // Short lists work on the caller's row-major image: the bricked copy costs
 // its allocation and release, two or three launches and a pass over the image
-// each way (20 us and more), which a list earns back by its samples (events x
-// planes).  Wall time per call, row-major against bricked, in us: forward
-// with TOF 32000 events 16 / 32 (128x128x48), 20 / 36 (200x200x96); without
-// TOF 16000 events 27 / 34 and 32000 42 / 40 (200x200x96).  Back with TOF
-// 16000 events 24 / 35, 34 / 58, 32000 44 / 48, 64 / 74, on one slice of 300x300
-// 48 / 44; without TOF 4000 events 18 / 34, 27 / 53, 16000 60 / 48, 94 / 89.
+// each way, which a list earns back by its samples (events x planes).  Back
+// projection earns it back sooner, as its atomics share fewer sectors of a
+// row-major image, the later the larger the image, and later with TOF, where
+// part of the planes counted have no weight.  Wall time per call,
+// row-major / bricked, in us (emissions of a phantom):
+//   forward, TOF: 32000 events 16 / 32 (128x128x48), 27 / 35 (200x200x96);
+//     no TOF: 16000 events 17 / 34, 51 / 45; 32000 29 / 37, 72 / 57
+//   back, TOF: 4000 events 14 / 22 (128x128x1), 17 / 26 (128x128x48), 24 / 51
+//     (200x200x96); 12000 37 / 37, 42 / 38, 62 / 72; 20000 60 / 53, 66 / 52, 99 / 93
+//     no TOF: 2000 events 14 / 23, 23 / 28, 35 / 56; 4000 25 / 24, 42 / 38, 64 / 72;
+//     8000 46 / 35, 79 / 57, 123 / 104
 static bool short_list(const GeomDev &g, long long n, long long samples) {
   return n < (1 << 15) && n * lmh::max_planes(g, W_BIN) <= samples;
 }
-constexpr long long kShortFwd = 1LL << 22, kShortBack = 1LL << 21;
+constexpr long long kShortFwd = 1LL << 22;
+static long long short_back(const GeomDev &g) {
+  return g.tof_on ? 600000 + lmh::nvox_of(g.n) / 6 : 400000 + lmh::nvox_of(g.n) / 10;
+}
 
 // Lists projected from the pair image (twice the memory), and in spatial
 // order (which costs some 60 us and 20 ns per event).  Without the order pairs
@@ -668,7 +676,7 @@ int lm_back(const lm_geom *G, const float *v, const int16_t *ev, int64_t n, floa
   LM_REQUIRE(n == 0 || (v && ev && img), LM_EINVAL, "NULL array");
   if (n == 0) return LM_OK;
   hipStream_t st = lmh::as_stream(stream);
-  if (short_list(g, n, kShortBack)) return launch_back(g, v, ev, n, img, st);
+  if (short_list(g, n, short_back(g))) return launch_back(g, v, ev, n, img, st);
   lmh::BrickImage b;
   if (int rc = b.alloc(g, st)) return rc;
   if (int rc = lmk::launch_to_layout(g.n, g.lay, 1, img, b.p, st)) return rc;
