@@ -256,14 +256,15 @@ static int bin_chunk(long long batch) {
 }
 
 namespace {
-// The temporaries of a batch.
+// The temporaries of a batch, with a table of ntab intervals.
 struct BackArrays {
   SegRay *rays;
   uint2 *item;
   unsigned *seg, *tot, *off, *nitems, *base;
   float *val;
+  float4 *tab = nullptr;
   lmh::Slab slab;
-  BackArrays(long long batch, long long pe, int ntiles) {
+  BackArrays(long long batch, long long pe, int ntiles, int ntab) {
     const int chunk = bin_chunk(batch);
     slab.add(&rays, batch);
     slab.add(&item, batch * pe / kItemMin + ntiles);
@@ -273,6 +274,7 @@ struct BackArrays {
     slab.add(&off, ntiles + 1);
     slab.add(&nitems, 2);
     slab.add(&base, (batch + chunk - 1) / chunk * ntiles);
+    if (ntab) slab.add(&tab, ntab);
   }
   BackArrays(const BackArrays &) = delete;  // the slab holds the addresses of the others
   BackArrays &operator=(const BackArrays &) = delete;
@@ -283,21 +285,22 @@ struct BackShape {
   TileGeom tg;
   int maxp;
   long long pe, batch;
-  BackShape(const GeomDev &g, long long n) : tg(tile_geom(g.n, kTL)), maxp(lmh::max_planes(g, W_BIN)) {
+  TofTab tt{};
+  int ntab;
+  BackShape(const GeomDev &g, long long n)
+      : tg(tile_geom(g.n, kTL)), maxp(lmh::max_planes(g, W_BIN)), ntab(tof_table_size(g, tt)) {
     pe = segs_per_event(g, maxp, kTL);
     batch = std::min(std::min(n, 1LL << 30), kListSegBytes / (4 * pe));
     // very unequal voxel sides: too many tiles per event to plan for
     if (batch < kMinListEvents || tg.ntiles > kMaxListTiles || !segs_supported(g)) batch = 0;
   }
-  size_t bytes(const GeomDev &g, long long events) const {
-    return BackArrays(events, pe, tg.ntiles).slab.bytes() + (g.tof_on ? kTofTabMax * sizeof(float4) : 0);
-  }
+  size_t bytes(long long events) const { return BackArrays(events, pe, tg.ntiles, ntab).slab.bytes(); }
 };
 }  // namespace
 
 size_t back_tiles_min_bytes(const GeomDev &g, long long n) {
   const BackShape s(g, n);
-  return s.batch ? s.bytes(g, kMinListEvents) : 0;
+  return s.batch ? s.bytes(kMinListEvents) : 0;
 }
 
 int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const int4 *rec, long long n, float *img,
@@ -306,15 +309,15 @@ int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const
   const BackShape shape(g, n);
   long long batch = shape.batch;
   if (room != SIZE_MAX && batch) {
-    while (batch > kMinListEvents && shape.bytes(g, batch) > room)
+    while (batch > kMinListEvents && shape.bytes(batch) > room)
       batch = std::max(kMinListEvents, batch - batch / 16);
-    if (shape.bytes(g, batch) > room) batch = 0;
+    if (shape.bytes(batch) > room) batch = 0;
     else batch = (n + (n + batch - 1) / batch - 1) / ((n + batch - 1) / batch);  // equal ones
   }
   if (!batch) return LM_OK;
   const TileGeom tg = shape.tg;
   const int maxp = shape.maxp, chunk = bin_chunk(batch);
-  BackArrays a(batch, shape.pe, tg.ntiles);
+  BackArrays a(batch, shape.pe, tg.ntiles, shape.ntab);
   void *tmp = nullptr;
   {
     const hipError_t e = a.slab.alloc(st, &tmp);
@@ -324,10 +327,8 @@ int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const
     }
     LM_TRY_HIP(e);
   }
-  TofTab tt{};
-  float4 *tab = nullptr;
-  int rc = build_tof_table(g, tt, &tab, st);
-  const size_t lds = (size_t)tg.ntiles * sizeof(unsigned), tlds = tab ? tof_tab_size(tt) * sizeof(float4) : 0;
+  const int rc = shape.ntab ? fill_tof_table(g, shape.tt, a.tab, st) : LM_OK;
+  const size_t lds = (size_t)tg.ntiles * sizeof(unsigned), tlds = shape.ntab * sizeof(float4);
   hipError_t e = hipSuccess;
   for (long long o = 0; rc == LM_OK && e == hipSuccess && o < n; o += batch) {
     const int m = (int)std::min(batch, n - o);
@@ -343,15 +344,14 @@ int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const
                        a.seg);
 #define LM_LB(TM_)                                                                                                \
   hipLaunchKernelGGL((k_list_back<TM_>), dim3(kBackGrid), dim3(kBackBlock), tlds, st, g, tg, a.off, a.item,       \
-                     a.nitems, a.seg, a.rays, a.val, tt, tab, img)
+                     a.nitems, a.seg, a.rays, a.val, shape.tt, a.tab, img)
     if (!g.tof_on) LM_LB(kTofNone);
-    else if (tab) LM_LB(kTofTable);
+    else if (a.tab) LM_LB(kTofTable);
     else LM_LB(kTofErfc);
 #undef LM_LB
     e = hipGetLastError();
   }
-  if (tab) (void)hipFreeAsync(tab, st);  // release errors have no caller to go to
-  (void)hipFreeAsync(tmp, st);
+  (void)hipFreeAsync(tmp, st);  // a release error has no caller to go to
   if (rc != LM_OK) return rc;
   LM_TRY_HIP(e);
   queued = true;

@@ -117,6 +117,10 @@ int launch_fwd_lines(const GeomDev &g, const int *cyl, const float *x, const int
 // frees, or nullptr (no TOF, a table too large, or no memory for it: the
 // kernels then evaluate erfc).
 int build_tof_table(const GeomDev &g, TofTab &t, float4 **tab, hipStream_t st);
+// The same in parts, for callers with an allocation of their own: the table's
+// layout and intervals (0: no table), and its values.
+int tof_table_size(const GeomDev &g, TofTab &t);
+int fill_tof_table(const GeomDev &g, const TofTab &t, float4 *tab, hipStream_t st);
 // Plan-internal event records: int4 {id1, id2, k, s bits}.
 int launch_fwd_rec(const GeomDev &g, const float *x, const int4 *rec, long long n, float *out,
                    hipStream_t st);

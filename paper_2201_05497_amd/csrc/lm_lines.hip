@@ -813,12 +813,25 @@ static int lds_per_block(int &bytes) {
   return LM_OK;
 }
 
-int build_tof_table(const GeomDev &g, TofTab &t, float4 **tab, hipStream_t st) {
-  *tab = nullptr;
-  if (!g.tof_on) return LM_OK;
+int tof_table_size(const GeomDev &g, TofTab &t) {
+  if (!g.tof_on) return 0;
   t = tof_tab_layout(g);
   const int n = tof_tab_size(t);
-  if (n > kTofTabMax) return LM_OK;
+  return n > kTofTabMax ? 0 : n;
+}
+
+int fill_tof_table(const GeomDev &g, const TofTab &t, float4 *tab, hipStream_t st) {
+  const double vc = (g.half_win - 0.5 * g.tof_bin) * g.inv_sr2, D = g.tof_bin * g.inv_sr2;
+  const double inv_norm = 1.0 / (2.0 * std::erf(vc));
+  hipLaunchKernelGGL(k_tof_table, dim3((tof_tab_size(t) + 255) / 256), dim3(256), 0, st, t, vc, D, inv_norm, tab);
+  LM_TRY_HIP(hipGetLastError());
+  return LM_OK;
+}
+
+int build_tof_table(const GeomDev &g, TofTab &t, float4 **tab, hipStream_t st) {
+  *tab = nullptr;
+  const int n = tof_table_size(g, t);
+  if (n == 0) return LM_OK;
   const hipError_t e = hipMallocAsync((void **)tab, (size_t)n * sizeof(float4), st);
   if (e == hipErrorOutOfMemory) {
     *tab = nullptr;
@@ -826,11 +839,7 @@ int build_tof_table(const GeomDev &g, TofTab &t, float4 **tab, hipStream_t st) {
     return LM_OK;
   }
   LM_TRY_HIP(e);
-  const double vc = (g.half_win - 0.5 * g.tof_bin) * g.inv_sr2, D = g.tof_bin * g.inv_sr2;
-  const double inv_norm = 1.0 / (2.0 * std::erf(vc));
-  hipLaunchKernelGGL(k_tof_table, dim3((n + 255) / 256), dim3(256), 0, st, t, vc, D, inv_norm, *tab);
-  LM_TRY_HIP(hipGetLastError());
-  return LM_OK;
+  return fill_tof_table(g, t, *tab, st);
 }
 
 int launch_fwd_lines(const GeomDev &g, const int *cyl, const float *x, const int16_t *ev, const unsigned *order,
