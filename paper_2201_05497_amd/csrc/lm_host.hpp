@@ -149,6 +149,18 @@ class Slab {
     parts_.push_back({p, bytes_});
     bytes_ += std::max<size_t>(count, 1) * sizeof(T);
   }
+  // The same for the last part, whose middle is laid on an odd multiple of 64
+  // KB.  Float atomics into a small image, which events hit mostly in its
+  // middle, run at a rate that has a period of 128 KB in the image's address:
+  // fastest there, where the two halves of the middle seem to be on different
+  // memory channels (see lm_plan_create).
+  template <class T>
+  void add_centred(T **p, size_t count) {
+    add(p, count);
+    half_ = std::max<size_t>(count, 1) * sizeof(T) / 512 * 256;
+    bytes_ += 2 * kCentre;
+  }
+  static constexpr size_t kCentre = 64 << 10;
   // the most bytes that one part takes
   template <class T>
   static size_t padded(size_t count) {
@@ -161,6 +173,10 @@ class Slab {
     if (e != hipSuccess) {
       *base = nullptr;
       return e;
+    }
+    if (half_) {
+      const size_t middle = reinterpret_cast<size_t>(*base) + parts_.back().offset + half_;
+      parts_.back().offset += (3 * kCentre - middle % (2 * kCentre)) % (2 * kCentre);
     }
     for (const Part &q : parts_) {
       void *at = static_cast<char *>(*base) + q.offset;
@@ -175,7 +191,7 @@ class Slab {
     size_t offset;
   };
   std::vector<Part> parts_;
-  size_t bytes_ = 0;
+  size_t bytes_ = 0, half_ = 0;
 };
 
 // The plain projector calls run on a bricked copy of the caller's row-major

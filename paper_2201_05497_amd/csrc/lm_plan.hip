@@ -331,7 +331,8 @@ Sizes plan_sizes(const lmk::GeomDev &g, long long n, int nsub, long long ne, int
   using lmh::Slab;
   Sizes s;
   s.persistent = Slab::padded<int4>(n) + 5 * Slab::padded<float>(n) + Slab::padded<int>(n) +
-                 Slab::padded<int>(nsub + 1) + 7 * Slab::padded<float>(ne) + 2 * Slab::padded<float>(ne * ncomp);
+                 Slab::padded<int>(nsub + 1) + 7 * Slab::padded<float>(ne) + 2 * Slab::padded<float>(ne * ncomp) +
+                 (g.n[2] == 1 ? 2 * Slab::kCentre : 0);
   const size_t cap = hash_capacity(n);
   const size_t creation = Slab::padded<unsigned long long>(cap) + Slab::padded<unsigned>(cap) +
                           Slab::padded<unsigned>(n) + Slab::padded<float>(ne) +
@@ -479,31 +480,21 @@ int lm_plan_create(const lm_geom *G, const int16_t *ev, const float *s, int64_t 
     free_plan(p);
     return code;
   };
-  // The arrays of a small plan (up to 2^17 events and voxels) have allocations
-  // of their own, which cost little to release at this size (0.2 ms in all, a
-  // frame's 36 of 4 MB 4.7): the per-event data update, a few microseconds long,
-  // depends on how its arrays lie to each other (single slice of 128x128, 28
-  // subsets, epoch with arrays of their own against one allocation: 1e5 events
-  // 487 / 540 us, 1.3e5 611 / 556).
-  const bool small = N <= (1 << 17) && E <= (1 << 17);
+  // The data update of a single slice scatters all events into one small
+  // image: dz lies where its atomics are fast.  128x128, 28 subsets, epoch of
+  // 1e5 / 4e5 / 2e6 events with the middle of dz on an odd multiple of 64 KB 441
+  // / 880 / 3310 us, on an even one 490 / 1040 / 3780, in between 485 / 1020 /
+  // 3870.  Images of 64x64 to 300x300 otherwise: within 3 % either way.
   lmh::Slab arrays;
-  auto add = [&](auto **q, size_t count) {
-    if (!small) {
-      arrays.add(q, count);
-    } else if (rc == LM_OK) {
-      lmh::Slab own;
-      own.add(q, count);
-      rc = dalloc(p, own);
-    }
-  };
-  add(&p->rec, N);
-  for (float **q : {&p->S, &p->mu, &p->c, &p->P1, &p->tmp}) add(q, N);
-  add(&p->perm, N);
-  add(&p->off_d, n_sub + 1);
-  for (float **q : {&p->gimg, &p->T, &p->z, &p->zbar, &p->dz, &p->xint, &p->xalt}) add(q, E);
-  for (float **q : {&p->w, &p->wn}) add(q, E * p->ncomp);
-  if (rc == LM_OK && !small) rc = dalloc(p, arrays);
-  if (rc != LM_OK) return fail(rc);
+  arrays.add(&p->rec, N);
+  for (float **q : {&p->S, &p->mu, &p->c, &p->P1, &p->tmp}) arrays.add(q, N);
+  arrays.add(&p->perm, N);
+  arrays.add(&p->off_d, n_sub + 1);
+  for (float **q : {&p->gimg, &p->T, &p->z, &p->zbar, &p->xint, &p->xalt}) arrays.add(q, E);
+  for (float **q : {&p->w, &p->wn}) arrays.add(q, E * p->ncomp);
+  if (G->n[2] == 1) arrays.add_centred(&p->dz, E);
+  else arrays.add(&p->dz, E);
+  if ((rc = dalloc(p, arrays))) return fail(rc);
 
   // temporaries: hash table, slots, ones image (bricks)
   const unsigned long long cap = hash_capacity(N);
