@@ -1,0 +1,147 @@
+"""GPU parity on the kernel variants that the choice of a path leaves to few
+calls, each on a case whose sizes are checked against the rule that chooses
+it: erfc TOF weights and batch boundaries of the back projection by tile, the
+spatial order with TOF, the forward projection by line without TOF and of
+several rings on one slice, the sensitivity of lines longer than a chunk of
+planes.  Tolerances as for every projection (1e-5) and back projection
+(1e-4)."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import lmsynth
+import oracle
+from tests.helpers import img_err, proj_err, report, smooth_image
+
+pytestmark = pytest.mark.gpu
+
+PROJ_TOL = 1e-5
+BACK_TOL = 1e-4
+TABLE_MAX = 1024  # intervals of the TOF table
+
+
+@pytest.fixture(scope="module")
+def P():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2201_05497_amd as P
+    return P
+
+
+def _geometry(P, n, h, tof, n_cry, n_ring, nsigma=3.0, fwhm=30.0, depth=None):
+    half = 0.5 * np.asarray(n) * np.asarray(h)
+    depth = 2.0 * half[2] if depth is None else depth
+    sc = lmsynth.Scanner(n_cry, n_ring, 1.3 * float(np.hypot(half[0], half[1])), depth / n_ring if n_ring > 1 else 0.0)
+    args = (lmsynth.det_table(sc), n_cry, n_ring, n, h, 9, 12.0, fwhm, nsigma, tof)
+    p = lmsynth.Problem("t", sc, lmsynth.ImageGeom(n, h), lmsynth.TOF(9, 12.0, fwhm, nsigma, tof), 1, 1, 0.0)
+    return p, P.Geometry(*args, device="cuda"), oracle.Geometry(*args)
+
+
+def _table_size(nsigma, fwhm, tof_bin=12.0):
+    sigma = fwhm / (2.0 * math.sqrt(2.0 * math.log(2.0)))
+    return 64 * (nsigma / math.sqrt(2.0) + 0.5 * tof_bin / (sigma * math.sqrt(2.0)))
+
+
+def _max_planes(n, h, tof, nsigma=3.0, fwhm=30.0, tof_bin=12.0):
+    if not tof:
+        return max(n)
+    sigma = fwhm / (2.0 * math.sqrt(2.0 * math.log(2.0)))
+    return min(math.ceil(2.0 * (nsigma * sigma + 0.5 * tof_bin) / min(h)) + 3, max(n))
+
+
+@pytest.mark.parametrize("n", [(40, 37, 20), (61, 47, 1)])
+def test_back_by_tile_with_erfc_weights(P, n):
+    assert _table_size(24.0, 30.0) > TABLE_MAX
+    p, Gg, Go = _geometry(P, n, (2.0, 2.0, 2.0), True, 96, 1 if n[2] == 1 else 12, nsigma=24.0)
+    ev = lmsynth.random_events(p, (1 << 15) + 19, seed=111, min_sep=1)
+    v = np.random.default_rng(112).uniform(-1, 1, len(ev)).astype(np.float32)
+    got = P.lm_back(Gg, torch.as_tensor(v, device="cuda"), Gg.events(ev)).cpu().numpy()
+    e = img_err(got, oracle.back(Go, v.astype(np.float64), ev))
+    report(f"back by tile, erfc {n}", events=len(ev), err=e)
+    assert e <= BACK_TOL
+
+
+def test_back_by_tile_around_batch_boundaries(P):
+    """A list of three batches whose values are zero except around the
+    boundaries of the batches (2^28 segment numbers each)."""
+    n, h = (128, 127, 48), (2.0, 2.0, 2.0)
+    te = 16
+    # chunks of planes times the tiles beside them (19 voxels reach 3 tiles of 16), the most of any axis
+    per_event = max((n[a] + te - 2) // te + 1 for a in range(3)) * 3 * 3
+    batch = (1 << 28) // per_event
+    p, Gg, Go = _geometry(P, n, h, False, 192, 24)
+    m = 2 * batch + 5000
+    ev = np.resize(lmsynth.random_events(p, 1_000_003, seed=113, min_sep=1), (m, 5))
+    at = np.concatenate([np.arange(c - 300, c + 300) for c in (batch, 2 * batch)] + [np.arange(300), np.arange(m - 300, m)])
+    vals = np.random.default_rng(114).uniform(0.1, 1, len(at)).astype(np.float32)
+    v = torch.zeros(m, device="cuda")
+    v[torch.as_tensor(at, device="cuda")] = torch.as_tensor(vals, device="cuda")
+    got = P.lm_back(Gg, v, Gg.events(ev)).cpu().numpy()
+    e = img_err(got, oracle.back(Go, vals.astype(np.float64), ev[at]))
+    report("back by tile, batch boundaries", events=m, batch=batch, err=e)
+    assert e <= BACK_TOL
+
+
+def test_forward_in_spatial_order_with_tof(P):
+    """Lists just below and above the events that are ordered (16 samples per
+    voxel, pair images beyond 16 MB): the same bits as short pieces."""
+    n, h = (181, 179, 65), (2.0, 2.6, 3.1)
+    edge = math.ceil(16 * n[0] * n[1] * n[2] / _max_planes(n, h, True))
+    assert edge > 1 << 19 and 8 * n[0] * n[1] * (n[2] + 1) > 16 << 20
+    p, Gg, Go = _geometry(P, n, h, True, 192, 12)
+    ev = lmsynth.random_events(p, edge + 1029, seed=115, min_sep=1)
+    bad = np.array([3, 1000, 700_001])
+    ev[bad] = [[192, 0, 3, 0, 0], [3, 12, 7, 0, 0], [-1, 0, 7, 0, 0]]
+    ev[5], ev[6] = [5, 0, 5, 3, 0], [5, 0, 5, 0, 0]  # along z; no line
+    x = smooth_image(Go.shape, 116)
+    xd, evd = torch.as_tensor(x, dtype=torch.float32, device="cuda"), Gg.events(ev)
+    for m in (edge - 1, edge, edge + 1029):
+        got = P.lm_fwd(Gg, xd, evd[:m].contiguous())
+        for a in (0, m // 2, m - 20_000):
+            assert torch.equal(P.lm_fwd(Gg, xd, evd[a:a + 20_000].contiguous()), got[a:a + 20_000])
+        g = got.cpu().numpy()
+        assert np.all(g[bad[bad < m]] == 0) and g[6] == 0
+        idx = np.setdiff1d(np.concatenate([np.arange(3000), np.arange(m - 3000, m)]), np.append(bad, 6))
+        emax, _ = proj_err(g[idx], oracle.fwd(Go, x, ev[idx]))
+        report("forward in order, TOF", events=m, err=emax)
+        assert emax <= PROJ_TOL
+
+
+@pytest.mark.parametrize("nz,n_ring,tof,nsigma", [
+    (36, 36, False, 3.0),   # without TOF, rings as planes
+    (1, 5, True, 3.0),      # several rings on one slice, table
+    (1, 5, True, 24.0),     # erfc
+    (1, 5, False, 3.0),
+])
+def test_forward_by_line(P, nz, n_ring, tof, nsigma):
+    """At least 64 events per transaxial line: both orientations, events along
+    z, of one crystal, out of range."""
+    p, Gg, Go = _geometry(P, (12, 13, nz), (2.6, 2.6, 2.6), tof, 24, n_ring, nsigma=nsigma,
+                          depth=max(2.6 * nz, 2.0 * n_ring))
+    assert (_table_size(nsigma, 30.0) > TABLE_MAX) == (nsigma > 3.0)
+    ev = lmsynth.random_events(p, 41_400, seed=117, min_sep=1)
+    rng = np.random.default_rng(118)
+    axial = np.stack([np.full(200, 5), rng.integers(0, n_ring, 200), np.full(200, 5), rng.integers(0, n_ring, 200),
+                      rng.integers(-4, 5, 200)], axis=1).astype(np.int16)
+    odd = np.array([[3, 0, 3, 0, 0], [24, 0, 3, 0, 0], [3, n_ring, 7, 0, 0], [3, 0, 7, 0, 5], [-1, 0, 7, 0, 0],
+                    [0, 0, 1, n_ring - 1, 0]], dtype=np.int16)
+    ev = np.concatenate([ev[:20000], axial, odd, ev[20000:]])
+    assert len(ev) >= max(64 * (24 * 23 // 2), 1 << 15)
+    x = smooth_image(Go.shape, 119)
+    got = P.lm_fwd(Gg, torch.as_tensor(x, device="cuda"), Gg.events(ev)).cpu().numpy()
+    bad = np.arange(20201, 20205)  # out of range: value 0, no oracle counterpart
+    assert np.all(got[bad] == 0.0) and got[20200] == 0.0
+    ok = np.setdiff1d(np.arange(len(ev)), bad)
+    emax, _ = proj_err(got[ok], oracle.fwd(Go, x, ev[ok]))
+    report(f"forward by line nz={nz} rings={n_ring} tof={tof} nsigma={nsigma}", events=len(ev), err=emax)
+    assert emax <= PROJ_TOL
+
+
+def test_sens_lines_of_two_chunks(P):
+    """Lines of up to 150 planes (chunks of 64) on several rings."""
+    p, Gg, Go = _geometry(P, (150, 141, 5), (2.0, 2.0, 2.0), True, 24, 3)
+    want = oracle.sens(Go)
+    e = img_err(P.lm_sens(Gg).cpu().numpy(), want)
+    report("sens, lines of three chunks", err=e)
+    assert want.max() > 0 and e <= BACK_TOL

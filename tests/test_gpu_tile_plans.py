@@ -1,6 +1,7 @@
 """GPU parity of plans whose data updates run by image tile, against the FP64
 oracle, at the edges of that path: images beyond the tiles that one binning
-workgroup counts.  That a plan has tile lists is seen from the device memory it
+workgroup counts, images around the number of tiles from which a workgroup has
+256 threads instead of 512, plans without TOF and with erfc TOF weights.  That a plan has tile lists is seen from the device memory it
 holds, against the same plan in subsets too small for them.  Tolerance as for
 every iterate."""
 import numpy as np
@@ -34,11 +35,11 @@ def _held(P, *args, **kw):
     return plan, pool.get(_USED) - before
 
 
-def _check(P, n, h, tof, subsets, seq, per_tile=4.05):
+def _check(P, n, h, tof, subsets, seq, per_tile=4.05, nsigma=3.0):
     half = 0.5 * np.asarray(n) * np.asarray(h)
     sc = lmsynth.Scanner(192, 24, 1.3 * float(np.hypot(half[0], half[1])), 2.0 * half[2] / 24)
-    args = (lmsynth.det_table(sc), 192, 24, n, h, 9, 12.0, 30.0, 3.0, tof)
-    p = lmsynth.Problem("t", sc, lmsynth.ImageGeom(n, h), lmsynth.TOF(9, 12.0, 30.0, 3.0, tof), 1, 1, 0.0)
+    args = (lmsynth.det_table(sc), 192, 24, n, h, 9, 12.0, 30.0, nsigma, tof)
+    p = lmsynth.Problem("t", sc, lmsynth.ImageGeom(n, h), lmsynth.TOF(9, 12.0, 30.0, nsigma, tof), 1, 1, 0.0)
     Gg, Go = P.Geometry(*args, device="cuda"), oracle.Geometry(*args)
     tiles = int(np.prod([(k + 7) // 8 for k in n]))
     m = int(per_tile * tiles) * subsets + 1
@@ -65,3 +66,14 @@ def _check(P, n, h, tof, subsets, seq, per_tile=4.05):
 def test_more_tiles_than_one_workgroup_counts(P):
     """40960 tiles, ragged edges: counted in two ranges of tiles."""
     _check(P, (505, 511, 75), (1.0, 1.0, 2.0), True, 2, [0, 1])
+
+
+@pytest.mark.parametrize("n,tiles,tof,nsigma", [
+    ((121, 127, 125), 4096, True, 3.0),   # 256 threads per tile, ragged
+    ((121, 113, 123), 3840, True, 3.0),   # 512
+    ((111, 97, 40), 910, False, 3.0),     # without TOF
+    ((51, 49, 23), 147, True, 24.0),      # a TOF kernel too wide for the table
+])
+def test_threads_per_tile_and_weights(P, n, tiles, tof, nsigma):
+    assert np.prod([(k + 7) // 8 for k in n]) == tiles
+    _check(P, n, (2.0, 2.0, 2.0), tof, 2, [0, 2, 1, 2, 0], nsigma=nsigma)
