@@ -9,11 +9,12 @@
 // events that reach it; then workgroups accumulate part of a tile's list in
 // LDS and add the tile to the image, one atomic request per 16 voxels.
 //
-// 1e7 events on 200x200x96: 25.2 -> 3.4 ms (counting 0.36, placing 0.65,
-// accumulating 2.6); 4 x 1e6 events on 128x128x48 with a TOF window of 43
+// 1e7 events on 200x200x96: 25.2 -> 3.4 ms (counting 0.38, placing 0.5 to
+// 0.65, accumulating 2.5); 4 x 1e6 events on 128x128x48 with a TOF window of 43
 // planes 6.5 -> 1.3 ms; 1e5 events without TOF on 121x127x47 0.64 -> 0.13 ms.
-// The accumulation is bound by its arithmetic (about 90 instructions per
-// 64 samples) and the placement by its scattered 4-byte stores.  Tiles of 8
+// The accumulation is bound by its LDS adds (the LDS is busy 74 % of its time)
+// and by the rays and values of its segments, which come from beyond the L2 at
+// 5.6 to 6.3 TB/s; the placement by its scattered 4-byte stores.  Tiles of 8
 // voxels per edge took 3.2 ms to accumulate and 1.7 ms to place the 1e7
 // events: an event has 14 segments in those, 6 in tiles of 16.
 #include <hip/hip_runtime.h>
@@ -237,10 +238,13 @@ long long segs_per_event(const GeomDev &g, int maxp, int te) {
   return most;
 }
 
-// Lists of at least this many events go by tile: the binning and the clearing
-// and adding of the tiles cost 50 to 70 us whatever the list, which the
-// per-event kernel (1.6 to 4.7 us per 1000 events, by grid and TOF) spends
-// on 2e4 to 4e4 events.
+// Lists of at least this many events go by tile: its calls, the binning and
+// the clearing and adding of the tiles cost 60 to 80 us whatever the list.  The
+// per-event kernel takes 1.2 to 3.4 us per 1000 events with TOF and 2.4 to 10
+// without, by grid, so it spends that on 2e4 to 6e4 events with TOF and 6e3
+// to 3e4 without.  33000 events, per event / by tile: 128x128x1 with TOF 81 /
+// 72, without 103 / 68; 64x64x16 of a small scanner 52 / 70 (the worst grid
+// measured), 99 / 70; 200x200x96 124 / 95, 287 / 118.
 constexpr long long kMinListEvents = 1 << 15;
 // Tiles of an image: the histogram of a binning workgroup, 4 bytes per tile,
 // is in LDS.
