@@ -371,8 +371,9 @@ int lm_plan_destroy(lm_plan *p);
  * image (row-major float[nz][ny][nx], e.g. from lm_sens); x: row-major
  * float image, x0 >= 0 on entry, the result on return.  All device
  * pointers, caller-owned.  Asynchronous on stream: temporaries (14 B per
- * event, 4 B per event of the largest subset, ten images) are allocated
- * and freed stream-ordered.  LM_EINVAL for bad arguments (nothing run),
+ * event, 4 B per event of the largest subset, ten images, and those of
+ * lm_back for subsets of 32768 events and more, per event without room for
+ * them) are allocated and freed stream-ordered.  LM_EINVAL for bad arguments (nothing run),
  * LM_ENOMEM when a temporary does not fit. */
 int lm_emtv(const lm_geom *G, const int16_t *ev, const float *s, int64_t n, int32_t n_subsets,
             int32_t n_iter, const float *g, float beta, int32_t denoise_iter, float *x, void *stream);
