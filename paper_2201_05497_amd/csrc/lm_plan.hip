@@ -490,10 +490,11 @@ int lm_plan_create(const lm_geom *G, const int16_t *ev, const float *s, int64_t 
   for (float **q : {&p->S, &p->mu, &p->c, &p->P1, &p->tmp}) arrays.add(q, N);
   arrays.add(&p->perm, N);
   arrays.add(&p->off_d, n_sub + 1);
-  for (float **q : {&p->gimg, &p->T, &p->z, &p->zbar, &p->xint, &p->xalt}) arrays.add(q, E);
+  for (float **q : {&p->gimg, &p->T, &p->z, &p->zbar}) arrays.add(q, E);
+  if (G->n[2] > 1) arrays.add(&p->dz, E);
+  for (float **q : {&p->xint, &p->xalt}) arrays.add(q, E);
   for (float **q : {&p->w, &p->wn}) arrays.add(q, E * p->ncomp);
   if (G->n[2] == 1) arrays.add_centred(&p->dz, E);
-  else arrays.add(&p->dz, E);
   if ((rc = dalloc(p, arrays))) return fail(rc);
 
   // temporaries: hash table, slots, ones image (bricks)
