@@ -530,20 +530,20 @@ int noalloc_scratch(hipStream_t st, float **out) {
 // each way, which a list earns back by its samples (events x planes).  Back
 // projection earns it back sooner, as its atomics share fewer sectors of a
 // row-major image, the later the larger the image, and later with TOF, where
-// part of the planes counted have no weight.  Wall time per call,
-// row-major / bricked, in us (emissions of a phantom):
-//   forward, TOF: 32000 events 16 / 32 (128x128x48), 27 / 35 (200x200x96);
+// part of the planes counted have no weight.  Wall time per call (emissions of a
+// phantom), row-major / bricked, in us:
+//   forward, TOF: 32000 events 14 / 32 (128x128x48), 27 / 35 (200x200x96);
 //     no TOF: 16000 events 17 / 34, 51 / 45; 32000 29 / 37, 72 / 57
-//   back, TOF: 4000 events 14 / 22 (128x128x1), 17 / 26 (128x128x48), 24 / 51
-//     (200x200x96); 12000 37 / 37, 42 / 38, 62 / 72; 20000 60 / 53, 66 / 52, 99 / 93
-//     no TOF: 2000 events 14 / 23, 23 / 28, 35 / 56; 4000 25 / 24, 42 / 38, 64 / 72;
-//     8000 46 / 35, 79 / 57, 123 / 104
+//   back, TOF: 8000 events 26 / 38 (128x128x1), 29 / 32 (128x128x48), 43 / 61
+//     (200x200x96); 12000 38 / 40, 42 / 38, 62 / 72; 20000 60 / 53, 67 / 57, 104 / 98
+//     no TOF: 4000 events 24 / 38, 42 / 38, 64 / 72; 6000 36 / 38, 61 / 54, 99 / 95;
+//     8000 46 / 38, 80 / 63, 123 / 104
 static bool short_list(const GeomDev &g, long long n, long long samples) {
   return n < (1 << 15) && n * lmh::max_planes(g, W_BIN) <= samples;
 }
 constexpr long long kShortFwd = 1LL << 22;
 static long long short_back(const GeomDev &g) {
-  return g.tof_on ? 600000 + lmh::nvox_of(g.n) / 6 : 400000 + lmh::nvox_of(g.n) / 10;
+  return g.tof_on ? 850000 + lmh::nvox_of(g.n) / 6 : 650000 + lmh::nvox_of(g.n) / 8;
 }
 
 // Lists projected from the pair image (twice the memory), and in spatial

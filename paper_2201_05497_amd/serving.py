@@ -118,7 +118,8 @@ class _SensCache:
 
 def footprint(req: Request) -> int:
     """Device bytes a request holds while admitted: its plan (including the
-    temporaries of plan creation), its events, contamination and image."""
+    temporaries of plan creation and initialisation), its events, contamination
+    and image."""
     n = len(req.events)
     return lm_plan_bytes(req.geom, n, req.n_subsets) + n * (10 + 4) + 4 * req.geom.nvox
 
