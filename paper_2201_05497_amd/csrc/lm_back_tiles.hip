@@ -221,16 +221,16 @@ bool segs_supported(const GeomDev &g) {
   return hmax <= kMaxVoxelRatio * hmin;
 }
 
-long long segs_per_event(const GeomDev &g, int maxp, int te) {
+long long segs_per_event(const GeomDev &g, int maxp, int te, int slack) {
   // chunks of te planes along axis a, and tiles a chunk can reach along axis
-  // b: the corners span at most (te - 1) h_a / h_b + 3 voxels, one more where
-  // float32 coordinates round across a voxel's edge (and at most the axis)
+  // b: the corners span at most ceil((te - 1) h_a / h_b) + 2 voxels and the
+  // slack (and at most the axis)
   long long most = 1;
   for (int a = 0; a < 3; ++a) {
     long long m = (std::min(maxp, g.n[a]) + te - 2) / te + 1;
     for (int b = 0; b < 3; ++b) {
       if (b == a) continue;
-      const long long span = (long long)std::floor((te - 1) * g.h[a] / g.h[b]) + 4;
+      const long long span = (long long)std::ceil((te - 1) * g.h[a] / g.h[b] - 1e-9) + 2 + slack;
       m *= std::min<long long>((span + te - 2) / te + 1, (g.n[b] + te - 1) / te);
     }
     most = std::max(most, m);
@@ -293,7 +293,7 @@ struct BackShape {
   int ntab;
   BackShape(const GeomDev &g, long long n)
       : tg(tile_geom(g.n, kTL)), maxp(lmh::max_planes(g, W_BIN)), ntab(tof_table_size(g, tt)) {
-    pe = segs_per_event(g, maxp, kTL);
+    pe = segs_per_event(g, maxp, kTL, 1);  // the batch's list is allocated by it
     batch = std::min(std::min(n, 1LL << 30), kListSegBytes / (4 * pe));
     // very unequal voxel sides: too many tiles per event to plan for
     if (batch < kMinListEvents || tg.ntiles > kMaxListTiles || !segs_supported(g)) batch = 0;

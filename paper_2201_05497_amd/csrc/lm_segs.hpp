@@ -224,8 +224,9 @@ __device__ __forceinline__ void add_segments(const GeomDev &g, const TileLane<TE
 bool segs_supported(const GeomDev &g);
 TileGeom tile_geom(const int n[3], int te);
 // Upper bound of the segments (tiles of edge te) of one event that visits at
-// most maxp planes.
-long long segs_per_event(const GeomDev &g, int maxp, int te);
+// most maxp planes; slack: voxels for the corners of float32 coordinates that
+// round across a voxel's edge (1 is enough).
+long long segs_per_event(const GeomDev &g, int maxp, int te, int slack);
 
 // Back projection of a caller's list (ev, or a plan's records rec when ev is
 // NULL) by tile, img += P^T v in the layout of g (lm_back_tiles.hip), in

@@ -413,7 +413,7 @@ size_t tile_bytes_bound(const GeomDev &g, long long n, int nsub) {
   const TileGeom tg = tile_geom(g.n, kTE);
   const long long nmax = (n + nsub - 1) / nsub;
   if (nmax < kMinEventsPerTile * tg.ntiles) return 0;
-  const long long per_event = segs_per_event(g, lmh::max_planes(g, W_BIN), kTE);
+  const long long per_event = segs_per_event(g, lmh::max_planes(g, W_BIN), kTE, 0);
   const long long nbin = (long long)nsub * tg.ntiles, nblk = (nbin + kScanB - 1) / kScanB;
   using lmh::Slab;
   const size_t kept = Slab::padded<unsigned>(n * per_event) + Slab::padded<long long>(nbin + 1) +

@@ -170,6 +170,29 @@ def test_plan_bytes_count_tile_lists_of_large_images():
     assert b[1].value - b[0].value > 200000 * 4
 
 
+def test_plan_bytes_of_cubic_voxels():
+    """A chunk of 8 planes of a ray reaches at most 9 voxels, two tiles, along
+    the other axes of cubic voxels, whatever their size in millimetres: 2 x 2
+    segments of 4 bytes per chunk and event."""
+    import ctypes
+    from paper_2201_05497_amd import _lib as L
+    if not os.path.exists(L.LIB_PATH):
+        pytest.skip("library not built")
+    lib = L.load()
+
+    def plan_bytes(h, n_ev):
+        g = L.LMGeom(0x1000, 672, 96, (ctypes.c_int32 * 3)(200, 200, 96), (ctypes.c_double * 3)(h, h, h),
+                     33, 9.0 * h, 23.0 * h, 3.0, 1)
+        b = ctypes.c_size_t(0)
+        assert lib.lm_plan_bytes(ctypes.byref(g), n_ev, 28, ctypes.byref(b)) == 0
+        return b.value
+
+    for h in (2.0, 2.6, 3.3):
+        per_event = (plan_bytes(h, 9_000_000) - plan_bytes(h, 8_500_000)) / 500_000
+        # 72 planes: 10 chunks; records and lists 44 bytes, rays of a subset 36 / 28
+        assert 10 * 4 * 4 <= per_event <= 10 * 4 * 4 + 50, (h, per_event)
+
+
 def test_sort_by_dominant_axis():
     """The large workload's input order: grouped by dominant axis (x, then
     y, then z), chronological inside each group, the same events and s."""
