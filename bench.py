@@ -116,14 +116,14 @@ KERNEL_SOURCES = {
 # kernel's sources at the time.  The summaries are under profiles/.
 PMC_TRAFFIC: dict = {
     # the data update by image tile: phase 1 (k_tile_fwd) + phase 2 (k_tile_back)
-    "data_update": {"fetch_bytes": 153300000, "write_bytes": 32600000, "sources": "4a0c1694caedcc3a",
+    "data_update": {"fetch_bytes": 153300000, "write_bytes": 32600000, "sources": "c87cd3286a7831a6",
         "profile": "profiles/epoch_3d_200x200x96_hbm_traffic.txt"},
     "tv": {"fetch_bytes": 106300000, "write_bytes": 77000000, "sources": "8227de5c540cce7f",
         "profile": "profiles/epoch_3d_200x200x96_hbm_traffic.txt"},
     # one lm_fwd / lm_back call over the 5e8-event long frame: all their kernels
     "fwd": {"fetch_bytes": 100500000000, "write_bytes": 18500000000, "sources": "1105d4206f44727a",
         "profile": "profiles/pass_3d_300x300x96_counters.txt"},
-    "back": {"fetch_bytes": 1046200000000, "write_bytes": 164900000000, "sources": "bcf53b01e93ac7b1",
+    "back": {"fetch_bytes": 1046200000000, "write_bytes": 164900000000, "sources": "5b4f03ed322c69bb",
         "profile": "profiles/pass_3d_300x300x96_counters.txt"},
 }
 
@@ -131,7 +131,7 @@ PMC_TRAFFIC: dict = {
 # VALU wavefront instructions per launch (rocprofv3 --pmc SQ_INSTS_VALU),
 # with the digest of the kernel's sources at the time.
 PMC_VALU: dict = {
-    "data_update": {"instr_per_launch": 17490000, "sources": "4a0c1694caedcc3a",
+    "data_update": {"instr_per_launch": 17490000, "sources": "c87cd3286a7831a6",
         "profile": "profiles/epoch_3d_200x200x96_l2_atomics_valu.txt"},
 }
 
