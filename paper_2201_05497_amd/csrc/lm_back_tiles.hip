@@ -316,9 +316,12 @@ int launch_back_tiles(const GeomDev &g, const float *v, const int16_t *ev, const
     while (batch > kMinListEvents && shape.bytes(batch) > room)
       batch = std::max(kMinListEvents, batch - batch / 16);
     if (shape.bytes(batch) > room) batch = 0;
-    else batch = (n + (n + batch - 1) / batch - 1) / ((n + batch - 1) / batch);  // equal ones
   }
   if (!batch) return LM_OK;
+  {  // equal batches
+    const long long count = (n + batch - 1) / batch;
+    batch = (n + count - 1) / count;
+  }
   const TileGeom tg = shape.tg;
   const int maxp = shape.maxp, chunk = bin_chunk(batch);
   BackArrays a(batch, shape.pe, tg.ntiles, shape.ntab);

@@ -64,7 +64,7 @@ def test_back_by_tile_with_erfc_weights(P, n):
 
 def test_back_by_tile_around_batch_boundaries(P):
     """A list of three batches whose values are zero except around the
-    boundaries of the batches (2^28 segment numbers each)."""
+    boundaries of the batches (equal ones of up to 2^28 segment numbers)."""
     n, h = (128, 127, 48), (2.0, 2.0, 2.0)
     te = 16
     # chunks of planes times the tiles beside them (19 voxels reach 3 tiles of 16), the most of any axis
@@ -72,6 +72,7 @@ def test_back_by_tile_around_batch_boundaries(P):
     batch = (1 << 28) // per_event
     p, Gg, Go = _geometry(P, n, h, False, 192, 24)
     m = 2 * batch + 5000
+    batch = -(-m // 3)
     ev = np.resize(lmsynth.random_events(p, 1_000_003, seed=113, min_sep=1), (m, 5))
     at = np.concatenate([np.arange(c - 300, c + 300) for c in (batch, 2 * batch)] + [np.arange(300), np.arange(m - 300, m)])
     vals = np.random.default_rng(114).uniform(0.1, 1, len(at)).astype(np.float32)
