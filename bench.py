@@ -123,7 +123,7 @@ PMC_TRAFFIC: dict = {
     # one lm_fwd / lm_back call over the 5e8-event long frame: all their kernels
     "fwd": {"fetch_bytes": 100500000000, "write_bytes": 18500000000, "sources": "1105d4206f44727a",
         "profile": "profiles/pass_3d_300x300x96_counters.txt"},
-    "back": {"fetch_bytes": 1046200000000, "write_bytes": 164900000000, "sources": "5b4f03ed322c69bb",
+    "back": {"fetch_bytes": 1045400000000, "write_bytes": 165500000000, "sources": "35fc53da6a75a36a",
         "profile": "profiles/pass_3d_300x300x96_counters.txt"},
 }
 

@@ -9,8 +9,8 @@
 // events that reach it; then workgroups accumulate part of a tile's list in
 // LDS and add the tile to the image, one atomic request per 16 voxels.
 //
-// 1e7 events on 200x200x96: 25.2 -> 3.4 ms (counting 0.38, placing 0.5 to
-// 0.65, accumulating 2.5); 4 x 1e6 events on 128x128x48 with a TOF window of 43
+// 1e7 events on 200x200x96: 25.2 -> 3.2 ms (counting 0.37, placing 0.50,
+// accumulating 2.5 under the profiler); 4 x 1e6 events on 128x128x48 with a TOF window of 43
 // planes 6.5 -> 1.3 ms; 1e5 events without TOF on 121x127x47 0.64 -> 0.13 ms.
 // The accumulation is bound by its LDS adds (the LDS is busy 74 % of its time)
 // and by the rays and values of its segments, which come from beyond the L2 at
